@@ -221,10 +221,9 @@ via_status via_pack_gate_up(const void *src, void *dst, int32_t d_ffn, int32_t d
 
 /* ---- prefill GEMM --------------------------------------------------------
  * C = X W^T for bf16 X [M, K] and W [N, K], fp32 accumulation and output:
- * the compute-bound tile kernel that runs every projection of a forward of
- * more than 512 rows (a prefill), exposed for measurement and tests.  (A
- * forward feeds it its fp32 activations as 2 bf16 terms, one pass each;
- * this call runs one.)
+ * the compute-bound tile kernel that runs the projections of a forward of
+ * many rows (a prefill), exposed for measurement and tests.  (A forward feeds
+ * it its fp32 activations as 2 bf16 terms; this call takes one.)
  *   X  device bf16, ceil(M/16)*16 rows, in the activation-fragment layout:
  *      element (m, k) is at 8-element group
  *      ((k/32) * ceil(M/16) + m/16) * 64 + ((k%32)/8) * 16 + m%16, offset k%8
@@ -283,9 +282,8 @@ via_status via_kv_seq_reserve(via_kv *kv, int32_t seq_id, int32_t n_ctx);
  * prefix x that the verification loop of Alg. 1 starts from (App. B.1
  * "Require"/"Ensure": the decoded sequence x grows from it); the paper does
  * not discuss the cache itself, so both verifiers keeping their own cache of
- * that prefix is this library's reading.  Forwards of more than 512 rows run
- * on the compute-bound tile GEMM; longer prompts are fed in chunks of the
- * handle's max_rows.  When the slim route starts with the full model's own
+ * that prefix is this library's reading.  Prompts longer than the handle's
+ * max_rows are fed in chunks of that many rows.  When the slim route starts with the full model's own
  * leading layers (route[i] == i for i < P, 0 < P < route length), those
  * layers run once: each chunk's slim forward starts at route index P from
  * the full forward's residual stream, and the K/V of layers 0..P-1 are
@@ -300,8 +298,9 @@ via_status via_prefill(via_model *m, via_kv *kv, int32_t seq_id, const int32_t *
  * prompts continue in later forwards), so the projections of a batch of
  * prompts run as one tall GEMM.  All-or-nothing: on any error no sequence
  * is attached (EINVAL for repeated or attached ids, ENOMEM when the pools
- * lack the blocks).  Same results as one via_prefill per sequence when
- * every forward has more than 512 rows either way. */
+ * lack the blocks).  The results are those of one via_prefill per sequence,
+ * to rounding: the projections sum in one order in forwards of more than
+ * 2048 rows, in an order that follows the row count below. */
 via_status via_prefill_batch(via_model *m, via_kv *kv, int32_t n_seqs, const int32_t *seq_ids, const int32_t *lens,
                              const int32_t *tokens, void *stream);
 /* Route index at which the last full-verifier forward of the current (or

@@ -1,30 +1,31 @@
-// Tall-skinny GEMMs of the verification forward.
+// GEMMs of the verification forward: P[split][M][N] = X[M, K-slice] * W[N,
+// K-slice]^T with M = fed rows and W packed.  gemm_path picks the kernel family
+// by the number of rows: weights streamed past registers (up to 32 rows), LDS-fed
+// row tiles, 256 x 256 prefill tiles; fp32 models and the bf16 head of up to 32
+// rows run the LDS-staged kernels.
 //
-// P[split][M][N] = X[M, K-slice] * W[N, K-slice]^T with M = fed rows (tens),
-// W (bf16, packed) streamed once from HBM.  A work-group of 8 waves owns a
-// 256-column tile, up to 64 rows and one K slice; each wave owns two
-// 16-column blocks and streams their weights over the whole slice, two
-// chunks of steps ahead of its multiply.  The activation fragments (X) of a
-// chunk are loaded once per work-group into LDS (double-buffered) and read
-// there by all eight waves, so X leaves L2 once per work-group and no
-// cross-wave reduction is needed.  The K slices of a tile ("splits") are
-// written as separate fp32 partial tiles and summed, in split order, by the
-// consumer kernel after the kernel boundary: handing partial sums between
-// work-groups inside one kernel would need a device-scope release, which
-// costs an L2 writeback on this GPU.  Every reduction has a fixed order, so
-// results are bitwise reproducible.
+// LDS-staged kernels: a work-group of 8 waves owns a 256-column tile, one row
+// group and one K slice; each wave owns two 16-column blocks and streams their
+// weights over the whole slice, two chunks of steps ahead of its multiply.  The
+// activation fragments (X) of a chunk are loaded once per work-group into LDS
+// (double-buffered) and read there by all eight waves, so X leaves L2 once per
+// work-group and no cross-wave reduction is needed.
 //
-// bf16 path: v_mfma_f32_16x16x32_bf16.  Lane l holds row/column l%16 and
+// The K slices of a tile ("splits") are written as separate fp32 partial tiles
+// and summed, in split order, by the consumer kernel after the kernel boundary:
+// handing partial sums between work-groups inside one kernel would need a
+// device-scope release, which costs an L2 writeback on this GPU.  Every
+// reduction has a fixed order, so results are bitwise reproducible.
+//
+// bf16 operands (v_mfma_f32_16x16x32_bf16): lane l holds row/column l%16 and
 // K sub-block (l/16)*8 .. +7 of each 32-wide step.  Weights are pre-packed
 // (via_pack_weight) and activations are written by their producer kernels
 // as fragments (afrag_group), so every global load of a wave reads one
 // contiguous 1 KB block and every LDS read is conflict-free.  fp32
-// activations enter the matrix cores as NT bf16 terms (x = hi + [mid +] lo),
-// NT = 3 keeping ~24 significant bits and NT = 2 ~16 (every projection
-// takes 2; the kernels also build for 3).  Output register r of
-// lane l is row (l/16)*4 + r, column l%16.  The head GEMM (split 1) reduces
-// its tile to per-row (max, second, sum-exp, argmax) partials and
-// draft-token logits in place.
+// activations enter the matrix cores as kTerms bf16 terms (x = hi + lo, ~16
+// significant bits).  Output register r of lane l is row (l/16)*4 + r, column
+// l%16.  The head reduces its tile to per-row (max, second, sum-exp, argmax)
+// partials and draft-token logits in place.
 // fp32 path: plain FMA on the vector ALUs (small models only).
 #include <hip/hip_ext.h>
 
@@ -263,20 +264,20 @@ __device__ __forceinline__ void merge3(float& mx, int& am, float& sc, float mx2,
 // Head tile epilogue, per head row: partial (max, second, sum-exp at the tile
 // max, argmax), the logit of each draft token inside the tile, and the
 // optional fp32 logits dump.  16 threads per row, 8 columns each.
-template <int MB>
+template <int MB, int TN = kTileN, int LDC = TN, int THR = kThreads>
 __device__ void epi_stats(const GemmArgs& a, int tile, int m0, const float* lds) {
-  const int grp = threadIdx.x >> 4, gl = threadIdx.x & 15;  // 32 groups of 16 threads
-  const int c0 = tile * kTileN;
-  for (int r = grp; r < 16 * MB; r += kThreads / 16) {
+  const int grp = threadIdx.x >> 4, gl = threadIdx.x & 15;  // THR / 16 groups of 16 threads
+  const int c0 = tile * TN;
+  for (int r = grp; r < 16 * MB; r += THR / 16) {
     const int m = m0 + r;
     if (m >= a.M) continue;  // uniform within the group
     // the row's final RMSNorm scale (the head is linear in it)
     const float rs = row_scale(a.ss, a.ss_stride, m, a.K, a.eps);
     float mx = -INFINITY, sc = -INFINITY;
     int am = 0x7fffffff;
-    constexpr int CPT = kTileN / 16;
+    constexpr int CPT = TN / 16;
     for (int c = gl * CPT; c < gl * CPT + CPT; ++c)
-      if (c0 + c < a.N) merge3(mx, am, sc, lds[r * kTileN + c] * rs, c0 + c, -INFINITY);
+      if (c0 + c < a.N) merge3(mx, am, sc, lds[r * LDC + c] * rs, c0 + c, -INFINITY);
     for (int o = 1; o < 16; o <<= 1) {
       const float mx2 = __shfl_xor(mx, o, 64), sc2 = __shfl_xor(sc, o, 64);
       const int am2 = __shfl_xor(am, o, 64);
@@ -284,7 +285,7 @@ __device__ void epi_stats(const GemmArgs& a, int tile, int m0, const float* lds)
     }
     float se = 0.f;
     for (int c = gl * CPT; c < gl * CPT + CPT; ++c)
-      if (c0 + c < a.N) se += expf((lds[r * kTileN + c] * rs - mx) * a.inv_T);
+      if (c0 + c < a.N) se += expf((lds[r * LDC + c] * rs - mx) * a.inv_T);
     for (int o = 1; o < 16; o <<= 1) se += __shfl_xor(se, o, 64);
     const int out = a.lm[m].out;
     if (gl == 0) {
@@ -296,11 +297,11 @@ __device__ void epi_stats(const GemmArgs& a, int tile, int m0, const float* lds)
     }
     if (gl < min(a.lm[m].n_drafts, kMaxChildren)) {
       const int tk = a.lm[m].draft_tok[gl];
-      if (tk >= c0 && tk < c0 + kTileN) a.draft_logit[a.lm[m].draft_idx[gl]] = lds[r * kTileN + tk - c0] * rs;
+      if (tk >= c0 && tk < c0 + TN) a.draft_logit[a.lm[m].draft_idx[gl]] = lds[r * LDC + tk - c0] * rs;
     }
     if (a.logits) {
       for (int c = gl * CPT; c < gl * CPT + CPT; ++c)
-        if (c0 + c < a.N) a.logits[(size_t)out * a.N + c0 + c] = lds[r * kTileN + c] * rs;
+        if (c0 + c < a.N) a.logits[(size_t)out * a.N + c0 + c] = lds[r * LDC + c] * rs;
     }
   }
 }
@@ -392,59 +393,21 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   }
 }
 
-// Gate/up projection with SwiGLU, h = silu(x W_g) * (x W_u) (the verifier's FFN).
-// The packed weight interleaves gate and up rows by 8 (launch_pack with ffn),
-// so 16-column block b holds gate and up columns of f = 8b .. 8b+7.  A
-// work-group owns a.nb consecutive blocks (one wave each; waves past nb only
-// stage X) over all of K, so no partial sums leave it: the tile goes to LDS
-// and the epilogue writes h for its (row, 8-f group)s as 2-term fragments,
-// the down projection's input.
-template <typename T, int MB, int C>
+// Gate/up projection with SwiGLU, h = silu(x W_g) * (x W_u) (the verifier's
+// FFN), fp32 models.  The packed weight interleaves gate and up rows by 8
+// (launch_pack with ffn), so 16-column block b holds gate and up columns of
+// f = 8b .. 8b+7.  A work-group owns a.nb consecutive blocks over all of K, so
+// no partial sums leave it: the tile goes to LDS and the epilogue writes h for
+// its (row, 8-f group)s, the down projection's input.
+template <int MB>
 __global__ __launch_bounds__(kThreads) void gemm_gate_up(GemmArgs a) {
-  constexpr int NT = sizeof(T) == 2 ? 2 : 1;
   constexpr int kCols = kWaves * 16;                        // widest tile (nb = 8)
-  constexpr int kLdsX = sizeof(T) == 2 ? 2 * TileShape<MB, NT, 1, C>::kXChunk * 16 : 0;
-  constexpr int kLdsT = 16 * MB * kCols * 4;
-  constexpr int kLds = kLdsX > kLdsT ? kLdsX : kLdsT;
-  __shared__ __align__(16) unsigned char smem[kLds];
-  float* lds = (float*)smem;
+  __shared__ __align__(16) float lds[16 * MB * kCols];
   const int nblocks = a.N >> 4;             // 16-column blocks (= F / 8 groups of h)
   const int blk0 = blockIdx.x * a.nb;
   const int m0 = blockIdx.y * 16 * MB;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int ncol = min(a.nb, nblocks - blk0) * 16;  // columns of this work-group
-  if constexpr (sizeof(T) == 2 && MB % 2 == 0 && MB >= 4) {
-    // 64 or more rows: each wave owns a pair of blocks on 32x32x16 MFMAs, so
-    // every X fragment read from LDS serves 32 columns (a.nb even; waves past
-    // nb / 2 only stage X).  One block per wave makes the LDS reads of X the
-    // limit.
-    f32x16 acc[MB / 2];
-    const bool active = 2 * wave < a.nb && blk0 + 2 * wave < nblocks;
-    tile_bf16<MB, NT, 2, C, true>(a, blk0 * 16, m0, 0, a.K >> 5, (uint4*)smem, acc, active);
-    __syncthreads();  // the X buffers become the output tile
-    if (active) {
-      // tile i, register r of lane l: row 32i + (r/4)*8 + (l/32)*4 + r%4, column wave*32 + l%32
-      const int cl = wave * 32 + (lane & 31), rl = (lane >> 5) * 4;
-#pragma unroll
-      for (int i = 0; i < MB / 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) lds[(i * 32 + (r >> 2) * 8 + rl + (r & 3)) * kCols + cl] = acc[i][r];
-    }
-  } else if constexpr (sizeof(T) == 2) {
-    f32x4 acc[1][MB];
-    const bool active = wave < a.nb && blk0 + wave < nblocks;
-    tile_bf16<MB, NT, 1, C>(a, blk0 * 16, m0, 0, a.K >> 5, (uint4*)smem, acc, active);
-    __syncthreads();  // the X buffers become the output tile
-    if (active) {
-      const int n = lane & 15, g = lane >> 4;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) lds[(mb * 16 + g * 4 + r) * kCols + wave * 16 + n] = acc[0][mb][r];
-    }
-  } else {
-    tile_f32<MB>(a, blk0 * 16, m0, 0, a.K, lds, ncol, kCols);
-  }
+  tile_f32<MB>(a, blk0 * 16, m0, 0, a.K, lds, ncol, kCols);
   __syncthreads();
   const int ngroups = ncol >> 4;
   for (int e = threadIdx.x; e < 16 * MB * ngroups; e += kThreads) {
@@ -458,7 +421,7 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up(GemmArgs a) {
       const float gt = t[i] * sc, up = t[8 + i] * sc;
       v[i] = gt / (1.0f + expf(-gt)) * up;
     }
-    put_afrag<sizeof(T) == 2, NT>(a.H, m, (blk0 + j) * 8, v, a.F >> 5, a.MBn);
+    put_afrag<false, 1>(a.H, m, (blk0 + j) * 8, v, a.F >> 5, a.MBn);
   }
 }
 
@@ -565,89 +528,86 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up_ki(GemmArgs a) {
 }
 
 // One entry point per projection, so kernel traces name the projection.
-#define VIA_GEMM_ENTRY(NAME, NT_BF16, STATS)                                              \
+#define VIA_GEMM_ENTRY(NAME, STATS)                                                       \
   template <typename T, int MB, int C>                                                   \
   __global__ __launch_bounds__(kThreads) void NAME(GemmArgs a) {                         \
-    gemm_body<T, MB, (sizeof(T) == 2 ? NT_BF16 : 1), kNBW, C, STATS>(a);                 \
+    gemm_body<T, MB, (sizeof(T) == 2 ? kTerms : 1), kNBW, C, STATS>(a);                  \
   }
-VIA_GEMM_ENTRY(gemm_qkv, kQkvTerms, false)
-VIA_GEMM_ENTRY(gemm_o, 2, false)
-VIA_GEMM_ENTRY(gemm_down, 2, false)
-VIA_GEMM_ENTRY(gemm_head, 2, true)
+VIA_GEMM_ENTRY(gemm_qkv, false)
+VIA_GEMM_ENTRY(gemm_o, false)
+VIA_GEMM_ENTRY(gemm_down, false)
+VIA_GEMM_ENTRY(gemm_head, true)
 #undef VIA_GEMM_ENTRY
 
-// X chunk steps: the double-buffered chunk stays within 144 KB of LDS and
-// splits evenly over the threads (C * NT * MB a multiple of 8).
-template <typename T, int MB, int NT, int NBW = kNBW>
+// X chunk steps: the chunk splits evenly over the threads (C * NT * MB a multiple of 8).
+template <typename T>
 constexpr int chunk_steps() {
-  if (sizeof(T) != 2) return 8;
-  if (MB > 4) return NT * MB == 24 ? 2 : 4;  // 96 or 128 rows: 72-128 KB of buffers
-  return (NBW == 1 && NT * MB <= 9) || (NT * MB) % 2 ? 8 : 4;
+  return sizeof(T) == 2 ? 4 : 8;
 }
 // With timing events the launch carries them in its dispatch, so they
 // bracket the kernel itself rather than the stream around it.
-#define VIA_GEMM_LAUNCH(NAME, NT_BF16)                                                       \
-  template <typename T>                                                                      \
-  void launch_##NAME(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {       \
-    constexpr int NT = sizeof(T) == 2 ? NT_BF16 : 1;                                         \
-    const int mb = gemm_rows_per_group(a.M) / 16;                                            \
-    const int mgroups = (a.M + 16 * mb - 1) / (16 * mb);                                     \
-    const dim3 grid(gemm_tiles(a.N) * a.ksplit * mgroups);                                   \
-    auto go = [&](auto kernel) {                                                             \
-      if (e0)                                                                                \
-        hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, e0, e1, 0, a);             \
-      else                                                                                   \
-        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a);                           \
-    };                                                                                       \
-    switch (mb) {                                                                            \
-      case 1: go(NAME<T, 1, chunk_steps<T, 1, NT>()>); break;                                \
-      case 2: go(NAME<T, 2, chunk_steps<T, 2, NT>()>); break;                                \
-      case 3: go(NAME<T, 3, chunk_steps<T, 3, NT>()>); break;                                \
-      case 4: go(NAME<T, 4, chunk_steps<T, 4, NT>()>); break;                                \
-      case 6: go(NAME<T, 6, chunk_steps<T, 6, NT>()>); break;                                \
-      default: go(NAME<T, 8, chunk_steps<T, 8, NT>()>); break;                               \
-    }                                                                                        \
+template <typename K>
+void launch_timed(K kernel, dim3 grid, int threads, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (e0)
+    hipExtLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, e0, e1, 0, a);
+  else
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a);
+}
+// bf16 models run only the head of up to 32 rows here (the other projections
+// and sizes have their own kernels); fp32 models run everything.
+#define VIA_GEMM_LAUNCH(NAME)                                                                     \
+  template <typename T>                                                                           \
+  void launch_##NAME(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {            \
+    const int mb = gemm_rows_per_group(a.M) / 16;                                                 \
+    const int mgroups = (a.M + 16 * mb - 1) / (16 * mb);                                          \
+    const dim3 grid(gemm_tiles(a.N) * a.ksplit * mgroups);                                        \
+    constexpr int C = chunk_steps<T>();                                                           \
+    auto go = [&](auto kernel) { launch_timed(kernel, grid, kThreads, a, s, e0, e1); };           \
+    if (mb == 1) return go(NAME<T, 1, C>);                                                        \
+    if (mb == 2) return go(NAME<T, 2, C>);                                                        \
+    if constexpr (sizeof(T) == 4) {                                                               \
+      if (mb == 3) return go(NAME<T, 3, C>);                                                      \
+      if (mb == 4) return go(NAME<T, 4, C>);                                                      \
+      if (mb == 6) return go(NAME<T, 6, C>);                                                      \
+      go(NAME<T, 8, C>);                                                                          \
+    }                                                                                             \
   }
-VIA_GEMM_LAUNCH(gemm_qkv, kQkvTerms)
-VIA_GEMM_LAUNCH(gemm_o, 2)
+VIA_GEMM_LAUNCH(gemm_qkv)
+VIA_GEMM_LAUNCH(gemm_o)
+VIA_GEMM_LAUNCH(gemm_down)
+VIA_GEMM_LAUNCH(gemm_head)
+#undef VIA_GEMM_LAUNCH
 
 // Gate/up with SwiGLU: grid (work-groups of a.nb blocks, row groups).
-template <typename T>
-void launch_gemm_gate_up(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  constexpr int NT = sizeof(T) == 2 ? 2 : 1;
+void launch_gate_up_f32(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const int mb = gemm_rows_per_group(a.M) / 16;
-  const int mgroups = (a.M + 16 * mb - 1) / (16 * mb);
-  GemmArgs b = a;
-  if (sizeof(T) == 2 && mb >= 4 && mb % 2 == 0)  // block pairs per wave: an even count, ~256 work-groups
-    b.nb = std::min(kWaves, 2 * std::max(1, ((a.N >> 4) + 511) / 512));
-  const dim3 grid(((b.N >> 4) + b.nb - 1) / b.nb, mgroups);
-  auto go = [&](auto kernel) {
-    if (e0)
-      hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, e0, e1, 0, b);
-    else
-      hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, b);
-  };
-  if constexpr (sizeof(T) == 2) {
-    if (mb <= 2) {  // up to 32 rows: K-interleaved waves
-      if (mb == 1)
-        go(gemm_gate_up_ki<1>);
-      else
-        go(gemm_gate_up_ki<2>);
-      return;
-    }
-  }
+  const dim3 grid(((a.N >> 4) + a.nb - 1) / a.nb, (a.M + 16 * mb - 1) / (16 * mb));
+  auto go = [&](auto kernel) { launch_timed(kernel, grid, kThreads, a, s, e0, e1); };
   switch (mb) {
-    case 1: go(gemm_gate_up<T, 1, chunk_steps<T, 1, NT, 1>()>); break;
-    case 2: go(gemm_gate_up<T, 2, chunk_steps<T, 2, NT, 1>()>); break;
-    case 3: go(gemm_gate_up<T, 3, chunk_steps<T, 3, NT, 1>()>); break;
-    case 4: go(gemm_gate_up<T, 4, chunk_steps<T, 4, NT, 2>()>); break;  // block pairs (bf16)
-    case 6: go(gemm_gate_up<T, 6, chunk_steps<T, 6, NT, 1>()>); break;
-    default: go(gemm_gate_up<T, 8, chunk_steps<T, 8, NT, 1>()>); break;
+    case 1: go(gemm_gate_up<1>); break;
+    case 2: go(gemm_gate_up<2>); break;
+    case 3: go(gemm_gate_up<3>); break;
+    case 4: go(gemm_gate_up<4>); break;
+    case 6: go(gemm_gate_up<6>); break;
+    default: go(gemm_gate_up<8>); break;
   }
 }
-VIA_GEMM_LAUNCH(gemm_down, 2)
-VIA_GEMM_LAUNCH(gemm_head, 2)
-#undef VIA_GEMM_LAUNCH
+void launch_gate_up_ki(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(((a.N >> 4) + a.nb - 1) / a.nb);
+  if (a.M <= 16)
+    launch_timed(gemm_gate_up_ki<1>, grid, kThreads, a, s, e0, e1);
+  else
+    launch_timed(gemm_gate_up_ki<2>, grid, kThreads, a, s, e0, e1);
+}
+void launch_staged_f32(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  switch (role) {
+    case GemmRole::kQkv: launch_gemm_qkv<float>(a, s, e0, e1); break;
+    case GemmRole::kO: launch_gemm_o<float>(a, s, e0, e1); break;
+    case GemmRole::kGateUp: launch_gate_up_f32(a, s, e0, e1); break;
+    case GemmRole::kDown: launch_gemm_down<float>(a, s, e0, e1); break;
+    case GemmRole::kHead: launch_gemm_head<float>(a, s, e0, e1); break;
+  }
+}
 
 
 // QKV, O and down projections of forwards of up to 32 rows (bf16): the
@@ -811,28 +771,22 @@ __global__ __launch_bounds__(kThreads) void gemm_ki_fixed(GemmArgs a) {
   }
 }
 
-template <int NT>
 void launch_ki_part(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   // split-major order: work-group i takes K split i % ksplit, so with the
   // round-robin dispatch of work-groups over the 8 XCDs each XCD's
   // work-groups share 8 / ksplit splits (one for 8 splits) and its L2 holds
   // only their slices of the activations
   const dim3 grid((((a.N >> 4) + a.nb - 1) / a.nb) * a.ksplit);
-  auto go = [&](auto kernel) {
-    if (e0)
-      hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, e0, e1, 0, a);
-    else
-      hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a);
-  };
+  auto go = [&](auto kernel) { launch_timed(kernel, grid, kThreads, a, s, e0, e1); };
   // fixed shapes (the 8B and 1B projections): even K splits and column blocks
   const int S = a.K >> 5, per = S / a.ksplit, nsw = per / kWaves;
   if (S % a.ksplit == 0 && per % kWaves == 0 && (a.N >> 4) % a.nb == 0) {
 #define VIA_KI_FIXED(NB_, NSW_)                                                   \
   if (a.nb == NB_ && nsw == NSW_) {                                              \
     if (a.M <= 16)                                                               \
-      go(gemm_ki_fixed<1, NT, NB_, NSW_, 2>);                                    \
+      go(gemm_ki_fixed<1, kTerms, NB_, NSW_, 2>);                                    \
     else                                                                         \
-      go(gemm_ki_fixed<2, NT, NB_, NSW_, 2>);                                    \
+      go(gemm_ki_fixed<2, kTerms, NB_, NSW_, 2>);                                    \
     return;                                                                      \
   }
     VIA_KI_FIXED(6, 4)
@@ -843,20 +797,9 @@ void launch_ki_part(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t 
 #undef VIA_KI_FIXED
   }
   if (a.M <= 16)
-    go(gemm_ki_part<1, NT>);
+    go(gemm_ki_part<1, kTerms>);
   else
-    go(gemm_ki_part<2, NT>);
-}
-
-template <typename T>
-void launch_role(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (role) {
-    case GemmRole::kQkv: launch_gemm_qkv<T>(a, s, e0, e1); break;
-    case GemmRole::kO: launch_gemm_o<T>(a, s, e0, e1); break;
-    case GemmRole::kGateUp: launch_gemm_gate_up<T>(a, s, e0, e1); break;
-    case GemmRole::kDown: launch_gemm_down<T>(a, s, e0, e1); break;
-    case GemmRole::kHead: launch_gemm_head<T>(a, s, e0, e1); break;
-  }
+    go(gemm_ki_part<2, kTerms>);
 }
 
 // ---------------------------------------------------------------- head stats
@@ -966,6 +909,11 @@ constexpr int kPfLds = kPfStages * kPfStage > kPfBM * kPfHStride * 4 ? kPfStages
 // 16 bytes per lane from base + voff to LDS at lds + 16 * lane (base wave-uniform)
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds) : "memory", "m0");
+}
+
+// The same, streamed past the caches.
+__device__ __forceinline__ void lds_dma16_stream(const void* base, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(lds) : "memory", "m0");
 }
 
 template <bool SWIGLU, bool PAIR>
@@ -1134,6 +1082,304 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_prefill(GemmArgs a, int nt) 
   }
 }
 
+// ----------------------------------------------------------- row-tile GEMM
+// bf16 projections and head of forwards between the weight-streaming kernels
+// (up to 32 rows) and the 256 x 256 prefill tiles: C[M, N] = sum over the two
+// activation terms of X_q[M, K] W[N, K]^T.  A work-group owns a tile of 16 MB
+// rows x 64 WN columns and one K split.  Everything reaches the matrix cores
+// through LDS: each 32-wide K step's X blocks (both terms) and W blocks are
+// copied verbatim by global_load_lds_dwordx4 into rings, and a step is read
+// into registers while the one before it is multiplied, so after a barrier no
+// product waits for LDS.  A wave multiplies 8 MB rows x 64 columns.
+//
+// What bounds it is the copies in flight: a compute unit returns them in order,
+// so X (an L2 hit) waits behind W (from HBM) and the two together move about
+// 46 GB/s per compute unit at ~110 KB in flight, all that the rings hold.
+// Half the waves copy W, SW trips deep, the other half X, SX deep, each
+// waiting on its own count before the barrier.
+//
+// WN = 2, KG = 2 (128 columns): up to 128 rows it keeps ~256 work-groups on the
+// weight stream, above it is taken where 256 columns would leave compute
+// units idle; waves 0-3 multiply the even and 4-7 the odd K steps and the two
+// halves are added in LDS.  WN = 4, KG = 1 (256 columns): the fewest copied
+// bytes per product.
+//
+// kPart writes one fp32 partial per split, kSwiglu (the gate/up projection)
+// writes h as in gemm_gate_up, kStats the head's row statistics.
+enum class RtEpi { kPart, kSwiglu, kStats };
+// Tile and K splits of one projection.
+struct RtPlan {
+  int rows, cols, ks;
+  double us;  // estimate
+};
+// The tile and split with the smallest estimate: rounds of tiles on 256 compute
+// units, and every split's partial written and read back at ~5 TB/s.  The time
+// of a round per 4096 of K is measured on the 8B gate/up projection (48, 96,
+// 128, 160 and 256 rows).  Above kFixedOrderRows rows there is one split and one
+// order of summation (that of the prefill tiles too), whatever the row count.
+RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
+  struct Tile {
+    int rows, cols;
+    double us;
+  };
+  static constexpr Tile kTiles[] = {{64, 128, 48.0}, {96, 128, 53.0}, {128, 128, 64.0}, {96, 256, 74.0}, {128, 256, 92.0}};
+  const bool split = role != GemmRole::kGateUp && role != GemmRole::kHead && M <= kFixedOrderRows;
+  RtPlan best{0, 0, 0, 0.0};
+  for (const Tile& tl : kTiles) {
+    if (M > kFixedOrderRows && tl.cols == 128) continue;  // its two K halves are another order
+    const int tiles = ((M + tl.rows - 1) / tl.rows) * ((N + tl.cols - 1) / tl.cols);
+    for (int ks = 1; ks <= (split ? 8 : 1) && (ks == 1 || K / 32 >= 16 * ks); ks *= 2) {
+      const double us = 10.0 + tl.us * ((tiles * ks + 255) / 256) * K / (4096.0 * ks) + 8e-6 / 5.0 * ks * M * (double)N;
+      if (!best.ks || us < best.us) best = RtPlan{tl.rows, tl.cols, ks, us};
+    }
+  }
+  return best;
+}
+// s_waitcnt operand: at most vm vector-memory and lgkm LDS operations outstanding
+constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | ((vm >> 4) << 14); }
+
+template <int MB, int WN, int KG, int SX, int SW>
+struct RtShape {
+  static constexpr int kBN = 64 * WN, kStride = kBN + 4;  // columns; fp32 per row of an output tile in LDS
+  static constexpr int kXTrip = KG * 2 * MB * 1024, kWTrip = KG * 4 * WN * 1024;  // bytes per trip (KG K steps)
+  static constexpr int kRing = SX * kXTrip + SW * kWTrip;
+  static constexpr int kTile = 16 * MB * kStride * 4;
+  static constexpr int kLds = kRing > kTile ? kRing : kTile;
+  static constexpr int kThreads = 128 * WN * KG;
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+  static_assert(MB % 2 == 0 && (2 * MB) % WN == 0 && (WN == 2 || WN == 4), "wave split");
+};
+
+template <int MB, int WN, int KG, int SX, int SW, RtEpi EPI>
+__global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
+  using SH = RtShape<MB, WN, KG, SX, SW>;
+  constexpr int HB = MB / 2;  // row blocks of a wave
+  constexpr int kThr = SH::kThreads, kBN = SH::kBN, kStride = SH::kStride;
+  __shared__ __align__(1024) unsigned char smem[SH::kLds];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int S = a.K >> 5, t64 = (a.N + 63) >> 6;
+  // XCD x (work-groups go round robin over the 8) takes a contiguous range of
+  // tiles; row tiles of one column tile are neighbours, so they share W in its L2
+  const int tiles_m = (a.M + 16 * MB - 1) / (16 * MB), tiles_n = (a.N + kBN - 1) / kBN;
+  const int ntiles = tiles_m * tiles_n * a.ksplit, perx = (ntiles + 7) >> 3;
+  const int tile = (blockIdx.x & 7) * perx + (blockIdx.x >> 3);
+  if (tile >= ntiles) return;  // uniform
+  const int tm = tile % tiles_m, tc = tile / tiles_m, split = tc / tiles_n, tn = tc - split * tiles_n;
+  const int m0 = tm * 16 * MB, n0 = tn * kBN;
+  // K steps of the split: KG of them per trip
+  const int per = (S + a.ksplit * KG - 1) / (a.ksplit * KG) * KG;
+  const int s_beg = min(S, split * per), s_end = min(S, s_beg + per);
+  const int T = (s_end - s_beg + KG - 1) / KG;
+  const uint32_t voff = lane * 16;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem);
+  const uint32_t ldsW = lds0 + SX * SH::kXTrip;
+  const size_t xstep = (size_t)a.MBn * 64;
+  const uint4* const X = (const uint4*)a.X;
+  // block b of a K step and term of X (rows past the fragments repeat the last
+  // block, columns past N the last tile: their products are never stored)
+  auto copy_x = [&](int ks, int q, int b, uint32_t dst) {
+    lds_dma16(X + ((size_t)q * S + ks) * xstep + (size_t)min((m0 >> 4) + b, a.MBn - 1) * 64, voff, dst);
+  };
+  auto copy_w = [&](int ks, int b, uint32_t dst) {
+    const int pt = min((n0 >> 6) + (b >> 2), t64 - 1);
+    lds_dma16_stream((const uint4*)a.W + ((size_t)pt * S + ks) * 256 + (b & 3) * 64, voff, dst);
+  };
+  // this wave's copies of trip t: a 64-column W tile, or a share of one term of
+  // X, of one K step (past the end the last K step again, into buffers nothing
+  // reads, so that every trip issues the same number)
+  constexpr int kNW = 4, kNX = 2 * MB / WN;
+  const bool copies_w = wave < KG * WN;
+  const int ckk = wave / WN % KG, cr = wave % WN;
+  auto issue = [&](int t, int sx, int sw) {
+    const int ks = min(s_beg + t * KG + ckk, s_end - 1);
+    if (copies_w) {
+#pragma unroll
+      for (int i = 0; i < kNW; ++i) copy_w(ks, cr * 4 + i, ldsW + ((sw * KG + ckk) * 4 * WN + cr * 4 + i) * 1024);
+    } else {
+      const int q = cr & 1, b0 = (cr >> 1) * kNX;
+#pragma unroll
+      for (int b = 0; b < kNX; ++b) copy_x(ks, q, b0 + b, lds0 + (((sx * KG + ckk) * 2 + q) * MB + b0 + b) * 1024);
+    }
+  };
+  f32x4 acc[HB][4];
+#pragma unroll
+  for (int i = 0; i < HB; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int kg = wave / (2 * WN), wm = wave / WN & 1, wn = wave % WN;
+  struct Ops {
+    uint4 x[2][HB], w[4];
+  };
+  auto read = [&](int sx, int sw, Ops& o) {
+    const uint4* xb = (const uint4*)(smem + ((sx * KG + kg) * 2 * MB + wm * HB) * 1024) + lane;
+    const uint4* wb = (const uint4*)(smem + SX * SH::kXTrip + ((sw * KG + kg) * WN + wn) * 4096) + lane;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o.w[j] = wb[j * 64];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < HB; ++i) o.x[q][i] = xb[(q * MB + i) * 64];
+  };
+  auto mma = [&](const Ops& o) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < HB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(o.x[q][i]), as_bf16x8(o.w[j]), acc[i][j], 0, 0, 0);
+  };
+  // every wave's copies of trip t + 1 have landed and its reads of trip t are
+  // back: the buffers of trip t take trip t + SX (SW)
+  auto arrive = [&]() {
+    if (copies_w)
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNW * (SW - 2), 0));
+    else
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNX * (SX - 2), 0));
+    __builtin_amdgcn_s_barrier();
+  };
+  static_assert(kNW * (SW - 1) < 64 && kNX * (SX - 1) < 64, "vmcnt");
+  constexpr int kReads = 2 * HB + 4, kMma = 8 * HB;  // per K step
+#define VIA_RT_PIN()                                                     \
+  _Pragma("unroll") for (int g_ = 0; g_ < kReads; ++g_) {               \
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); /* 1 LDS read */ \
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0); /* 2 MFMAs */    \
+  }                                                                      \
+  if constexpr (kMma > 2 * kReads) __builtin_amdgcn_sched_group_barrier(0x008, kMma - 2 * kReads, 0);
+  int sx = 0, sw = 0;  // ring positions of the trip in registers
+  auto next = [](int s, int n) { return s + 1 == n ? 0 : s + 1; };
+  Ops pa, pb;
+  // one trip: multiply `cur` (trip t), read trip t + 1 into `nxt`
+#define VIA_RT_TRIP(cur, nxt)                  \
+  {                                             \
+    arrive();                                   \
+    issue(t + (copies_w ? SW : SX), sx, sw);    \
+    sx = next(sx, SX);                          \
+    sw = next(sw, SW);                          \
+    read(sx, sw, nxt);                          \
+    mma(cur);                                   \
+    VIA_RT_PIN()                                \
+    ++t;                                        \
+  }
+  if (T > 0) {
+#pragma unroll
+    for (int p = 0; p < (SX > SW ? SX : SW); ++p)
+      if (copies_w ? p < SW : p < SX) issue(p, p % SX, p % SW);
+    // trip 0 in LDS: all but the SX (SW) - 1 youngest trips
+    if (copies_w)
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNW * (SW - 1), 15));
+    else
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNX * (SX - 1), 15));
+    __builtin_amdgcn_s_barrier();
+    read(0, 0, pa);
+    int t = 0;
+    for (; t + 2 < T;) {
+      VIA_RT_TRIP(pa, pb)
+      VIA_RT_TRIP(pb, pa)
+    }
+    // one or two trips left; the last one of an odd split has no second K step
+    const bool tail = s_beg + (T - 1) * KG + kg < s_end;
+    if (T - t == 2) {
+      VIA_RT_TRIP(pa, pb)
+      if (tail) mma(pb);
+    } else if (tail) {
+      mma(pa);
+    }
+  }
+#undef VIA_RT_TRIP
+#undef VIA_RT_PIN
+  __builtin_amdgcn_s_waitcnt(0);  // the trailing copies land before LDS is reused or the work-group ends
+  const int n = lane & 15, g = lane >> 4;
+  float* tl = (float*)smem;
+  if constexpr (EPI == RtEpi::kPart && KG == 1) {
+    float* P = a.part + (size_t)split * a.M * a.N;
+#pragma unroll
+    for (int i = 0; i < HB; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int col = n0 + wn * 64 + j * 16 + n;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + (wm * HB + i) * 16 + g * 4 + r;
+          if (m < a.M && col < a.N) P[(size_t)m * a.N + col] = acc[i][j][r];
+        }
+      }
+    return;
+  }
+  __syncthreads();
+  auto cell = [&](int i, int j, int r) -> float& {
+    return tl[((wm * HB + i) * 16 + g * 4 + r) * kStride + wn * 64 + j * 16 + n];
+  };
+  if (KG == 1 || kg == 1) {
+#pragma unroll
+    for (int i = 0; i < HB; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) cell(i, j, r) = acc[i][j][r];
+  }
+  __syncthreads();
+  if constexpr (KG == 2) {
+    if (kg == 0) {  // even K steps + odd K steps
+#pragma unroll
+      for (int i = 0; i < HB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) cell(i, j, r) = acc[i][j][r] + cell(i, j, r);
+    }
+    __syncthreads();
+  }
+  if constexpr (EPI == RtEpi::kPart) {
+    float* P = a.part + (size_t)split * a.M * a.N;
+    const int c = threadIdx.x % (kBN / 4) * 4;
+    for (int r = threadIdx.x / (kBN / 4); r < 16 * MB; r += kThr / (kBN / 4)) {
+      const int m = m0 + r, col = n0 + c;
+      if (m >= a.M) break;
+      if (col < a.N) *(float4*)(P + (size_t)m * a.N + col) = *(const float4*)(tl + r * kStride + c);  // N % 4 == 0
+    }
+  } else if constexpr (EPI == RtEpi::kSwiglu) {
+    for (int e = threadIdx.x; e < 16 * MB * (kBN / 16); e += kThr) {
+      const int r = e % (16 * MB), j = e / (16 * MB), m = m0 + r, f = (n0 >> 1) + j * 8;
+      if (m >= a.M || f >= a.F) continue;
+      const float* t = tl + r * kStride + j * 16;
+      const float sc = row_scale(a.ss, a.ss_stride, m, a.K, a.eps);  // RMSNorm of the input row
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float gt = t[i] * sc, up = t[8 + i] * sc;
+        v[i] = gt / (1.0f + expf(-gt)) * up;
+      }
+      put_afrag<true, 2>(a.H, m, f, v, a.F >> 5, a.MBn);
+    }
+  } else {
+    epi_stats<MB, kBN, kStride, kThr>(a, tn, m0, tl);
+  }
+}
+
+void launch_row_tile(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const RtPlan p = row_tile_plan(role, a.M, a.N, a.K);
+  const int ntiles = ((a.M + p.rows - 1) / p.rows) * ((a.N + p.cols - 1) / p.cols) * a.ksplit;
+  const dim3 grid((ntiles + 7) / 8 * 8);
+  auto pick = [&](auto part, auto swiglu, auto stats) {
+    launch_timed(role == GemmRole::kGateUp ? swiglu : role == GemmRole::kHead ? stats : part, grid, 512, a, s, e0, e1);
+  };
+#define VIA_RT_PICK(...)                                                                        \
+  pick(gemm_row_tile<__VA_ARGS__, RtEpi::kPart>, gemm_row_tile<__VA_ARGS__, RtEpi::kSwiglu>,   \
+       gemm_row_tile<__VA_ARGS__, RtEpi::kStats>)
+  if (p.cols == 256 && p.rows == 96)
+    VIA_RT_PICK(6, 4, 1, 5, 6);
+  else if (p.cols == 256)
+    VIA_RT_PICK(8, 4, 1, 5, 5);
+  else if (p.rows == 64)
+    VIA_RT_PICK(4, 2, 2, 3, 6);
+  else if (p.rows == 96)
+    VIA_RT_PICK(6, 2, 2, 4, 3);
+  else
+    VIA_RT_PICK(8, 2, 2, 3, 4);
+#undef VIA_RT_PICK
+}
+
 void launch_prefill(const GemmArgs& a, int nt, bool swiglu, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const int ntiles = ((a.M + kPfBM - 1) / kPfBM) * ((a.N + kPfBN - 1) / kPfBN);
   const dim3 grid((ntiles + 7) / 8 * 8);
@@ -1143,10 +1389,8 @@ void launch_prefill(const GemmArgs& a, int nt, bool swiglu, hipStream_t s, hipEv
     else
       hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, a, nt);
   };
-  if (swiglu && nt == 2)
+  if (swiglu)
     go(gemm_prefill<true, true>);
-  else if (swiglu)
-    go(gemm_prefill<true, false>);
   else if (nt == 2)
     go(gemm_prefill<false, true>);
   else
@@ -1173,8 +1417,23 @@ int gate_up_blocks_per_group(int F) {
 
 int gemm_tiles(int N) { return (N + kTileN - 1) / kTileN; }
 
-bool gemm_uses_ki(GemmRole role, int M, int N) {
-  return (role == GemmRole::kQkv || role == GemmRole::kO || role == GemmRole::kDown) && M <= 32 && N % 16 == 0;
+GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K) {
+  if (!bf16) return GemmPath::kStaged;
+  if (M <= 32) return role == GemmRole::kHead ? GemmPath::kStaged : GemmPath::kStream;
+  if (M <= 128 || role == GemmRole::kHead) return GemmPath::kRowTile;
+  // 256 x 256 tiles take 178 us a round per 4096 of K, less than the two rounds
+  // of row tiles they stand for, when there are enough of them
+  const int tiles = ((M + kPfBM - 1) / kPfBM) * ((N + kPfBN - 1) / kPfBN);
+  const double us = 20.0 + 178.0 * ((tiles + 255) / 256) * K / 4096.0 + 8e-6 / 5.0 * M * (double)N;
+  return us < row_tile_plan(role, M, N, K).us ? GemmPath::kPrefill : GemmPath::kRowTile;
+}
+
+int gemm_splits(GemmRole role, int M, int N, int K) { return row_tile_plan(role, M, N, K).ks; }
+
+int gemm_head_tiles(bool bf16, int M, int N, int K) {
+  if (gemm_path(bf16, GemmRole::kHead, M, N, K) != GemmPath::kRowTile) return gemm_tiles(N);
+  const int cols = row_tile_plan(GemmRole::kHead, M, N, K).cols;
+  return (N + cols - 1) / cols;
 }
 
 void gemm_ki_plan(int N, int K, int* nb, int* ksplit) {
@@ -1196,27 +1455,28 @@ int gemm_padded_rows(int M) {
   return (M + g - 1) / g * g;
 }
 
-bool gemm_is_prefill(bool bf16, int M) { return bf16 && M > kPrefillMinRows; }
-
 void launch_gemm(bool bf16, GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (role != GemmRole::kHead && gemm_is_prefill(bf16, a.M)) {
-    // many rows: the compute-bound tile kernel (one partial, ksplit 1; the
-    // gate/up projection writes h itself)
-    const int nt = role == GemmRole::kQkv ? kQkvTerms : 2;
-    launch_prefill(a, nt, role == GemmRole::kGateUp, s, e0, e1);
-    return;
+  switch (gemm_path(bf16, role, a.M, a.N, a.K)) {
+    case GemmPath::kPrefill:
+      // the compute-bound tile kernel (one partial, ksplit 1; the gate/up projection writes h itself)
+      launch_prefill(a, 2, role == GemmRole::kGateUp, s, e0, e1);
+      break;
+    case GemmPath::kRowTile:
+      launch_row_tile(role, a, s, e0, e1);
+      break;
+    case GemmPath::kStream:
+      if (role == GemmRole::kGateUp)
+        launch_gate_up_ki(a, s, e0, e1);
+      else
+        launch_ki_part(a, s, e0, e1);
+      break;
+    case GemmPath::kStaged:
+      if (bf16)
+        launch_gemm_head<uint16_t>(a, s, e0, e1);
+      else
+        launch_staged_f32(role, a, s, e0, e1);
+      break;
   }
-  if (bf16 && a.nb > 0 && gemm_uses_ki(role, a.M, a.N)) {
-    if (role == GemmRole::kQkv)
-      launch_ki_part<kQkvTerms>(a, s, e0, e1);
-    else
-      launch_ki_part<2>(a, s, e0, e1);
-    return;
-  }
-  if (bf16)
-    launch_role<uint16_t>(role, a, s, e0, e1);
-  else
-    launch_role<float>(role, a, s, e0, e1);
 }
 
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s) { launch_prefill(a, 1, false, s, nullptr, nullptr); }

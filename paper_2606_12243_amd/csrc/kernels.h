@@ -34,33 +34,43 @@ struct GemmArgs {
   float eps;
 };
 
-// Projection a GEMM computes.  Each has its own kernel entry point; the QKV
-// input carries kQkvTerms bf16 terms per fp32 activation, the others 2; the head
-// reduces its tiles to row statistics instead of writing partials; the
-// gate/up projection runs over all of K and applies SwiGLU itself.
+// Projection a GEMM computes: the head reduces its tiles to row statistics
+// instead of writing partials; the gate/up projection runs over all of K and
+// applies SwiGLU itself.
 enum class GemmRole { kQkv, kO, kGateUp, kDown, kHead };
-// bf16 terms per fp32 activation at the QKV projection's input (the others take 2).
-constexpr int kQkvTerms = 2;
+// bf16 terms per fp32 activation at every projection's input (bf16 models).
+constexpr int kTerms = 2;
 // e0/e1 (both or neither): timing events recorded at the kernel's own start
 // and end.
 void launch_gemm(bool bf16, GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                  hipEvent_t e1 = nullptr);
-// Forwards of more rows than this run their projections (bf16 models) on the
-// compute-bound prefill GEMM, which writes one partial (ksplit must be 1).
-// Below it the weight-streaming GEMMs, at most 4 passes of 128-row groups
-// over the weights, cost less than 256 x 256 tiles too few to fill the GPU.
-constexpr int kPrefillMinRows = 512;
-bool gemm_is_prefill(bool bf16, int M);
+// Kernel family of an [M, K] x [N, K]^T projection.
+//   kStream   bf16, up to 32 rows: weights stream past registers; QKV, O and
+//             down in work-groups of a.nb 16-column blocks of one of a.ksplit
+//             K splits (gemm_ki_plan), gate/up over all of K
+//   kRowTile  bf16, 33 rows and more (the head's only kernel there): LDS-fed
+//             tiles of 64 to 128 rows x 128 or 256 columns, gemm_splits K splits
+//   kPrefill  bf16, enough rows to fill the GPU with 256 x 256 tiles (one partial)
+//   kStaged   fp32 models, and the bf16 head of up to 32 rows
+enum class GemmPath { kStream, kRowTile, kPrefill, kStaged };
+GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K);
+// K splits (partial products) of the kRowTile kernel.
+int gemm_splits(GemmRole role, int M, int N, int K);
+// Forwards of more rows than this sum every projection in one order, so that a
+// row's result does not depend on the rows it is batched with.
+constexpr int kFixedOrderRows = 2048;
+// Forwards of more rows than this take the many-row forms of the residual
+// update and the QKV finish.
+constexpr int kManyRows = 512;
+// Column tiles the head of M rows reduces its statistics to.
+int gemm_head_tiles(bool bf16, int M, int N, int K);
 // Plain bf16 product a.part[M, N] = X[M, K] W[N, K]^T (one activation term)
 // on the prefill GEMM.
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
-// Column tiles (256 wide) of an N-column GEMM.
+// Column tiles (256 wide) of an N-column kStaged GEMM.
 int gemm_tiles(int N);
-// QKV, O and down projections of forwards of up to 32 rows (bf16 models, N a
-// multiple of 16) run on the K-interleaved split-K kernel, whose work-groups
-// own a.nb 16-column blocks of one of a.ksplit K splits; gemm_ki_plan picks
-// both for an [N, K] weight (about 256 work-groups).
-bool gemm_uses_ki(GemmRole role, int M, int N);
+// Blocks per work-group and K splits of the kStream kernels for an [N, K]
+// weight (about 256 work-groups).
 void gemm_ki_plan(int N, int K, int* nb, int* ksplit);
 // Rows per GEMM work-group for M rows (16, 32, 48, 64, 96 or 128).
 int gemm_rows_per_group(int M);
@@ -76,7 +86,7 @@ void launch_pack(bool bf16, const void* src, void* dst, int rows, int cols, int 
 int gate_up_blocks_per_group(int F);
 
 // X[m] += sum_s P[s][m] (split order; P may be null); x * g is written as
-// activation fragments (`terms` bf16 terms, or fp32), to fragment row
+// activation fragments (kTerms bf16 terms, or fp32), to fragment row
 // rows[m].lm when `rows` is given (rows with lm < 0 skipped), and the sums of
 // x^2 over column chunks to ss[chunk * ss_stride + row]: the consumer of the
 // next projection multiplies its output row by row_scale() (RMSNorm).
@@ -84,7 +94,7 @@ int gate_up_blocks_per_group(int F);
 // erows[m].xs when erows is given (skipped where xs < 0), else to row m.
 // E (nullable, model dtype [vocab, d]): X[m] is first set to the embedding
 // row of token erows[m].tok (P is then ignored).
-void launch_resid_add(bool bf16, int terms, float* X, const float* P, int ksplit, int M, int d, const void* g,
+void launch_resid_add(bool bf16, float* X, const float* P, int ksplit, int M, int d, const void* g,
                       void* Y, int MBn, const RowInfo* rows, float* ss, int ss_stride, hipStream_t s,
                       float* Xcopy = nullptr, const void* E = nullptr, const RowInfo* erows = nullptr);
 

@@ -142,42 +142,61 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
   put_afrag<BF16, NT>(Y, out, k0, v, d >> 5, MBn);
 }
 
-// Many-row form of the residual update (forwards of more than
-// kPrefillMinRows rows, one partial P, no head rows or embedding gather):
-// a work-group of 64 threads owns one 16-row block of the fragment layout and
-// one kNormChunk of columns.  Thread t takes row t % 16 and, in each of the
-// chunk's K32 steps s, the 8-column group t / 16, so every fragment store of
-// the wave writes one contiguous 1 KB block (the one-row form writes 16 bytes
-// every 256).  The values are those of resid_add_kernel: the 8-column group
-// 4 s + t / 16 is that kernel's thread, and its partial sums of squares are
-// added in that kernel's wave_sum order (three levels within the thread, two
-// across lanes).
-template <int NT>
-__global__ __launch_bounds__(64) void resid_add_rows_kernel(float* X, const float* P, int M, int d, const uint16_t* g,
-                                                            void* Y, int MBn, float* ss, int ss_stride, float* Xcopy) {
-  constexpr int kSteps = kNormChunk / 32;
-  const int chunk = blockIdx.x, t = threadIdx.x, r = t & 15, j = t >> 4;
+// Many-row form of the residual update (KS partials P, no head rows or
+// embedding gather): a work-group of four waves owns one 16-row block of the
+// fragment layout and one kNormChunk of columns.  Thread t of a wave takes row
+// t % 16 and, in each of the wave's K32 steps s = wave + 4 i, the 8-column group
+// t / 16, so every fragment store of a wave writes one contiguous 1 KB block
+// (the one-row form writes 16 bytes every 256).  The values are those of
+// resid_add_kernel: the 8-column group 4 s + t / 16 is that kernel's thread,
+// and its partial sums of squares are added in that kernel's wave_sum order
+// (two levels within the thread, two across waves, two across lanes).
+template <int NT, int KS>
+__global__ __launch_bounds__(256) void resid_add_rows_kernel(float* X, const float* P, int M, int d, const uint16_t* g,
+                                                             void* Y, int MBn, float* ss, int ss_stride, float* Xcopy,
+                                                             const RowInfo* erows) {
+  constexpr int kPer = kNormChunk / 32 / 4;  // K32 steps of a wave
+  static_assert(kPer == 4, "the sum order below is for 16 steps");
+  __shared__ float part[4][64];
+  const int chunk = blockIdx.x, w = threadIdx.x >> 6, t = threadIdx.x & 63, r = t & 15, j = t >> 4;
   const int m = blockIdx.y * 16 + r;
   const bool live = m < M;
-  float p[kSteps];
+  const size_t stride = (size_t)M * d;
+  if (Xcopy && live) {
+    const int xr = erows ? erows[m].xs : m;
+    Xcopy = xr < 0 ? nullptr : Xcopy + (size_t)xr * d;
+  }
+  float p[kPer];
 #pragma unroll
-  for (int st = 0; st < kSteps; ++st) {
-    const int k0 = chunk * kNormChunk + st * 32 + j * 8;
-    p[st] = 0.f;
+  for (int i = 0; i < kPer; ++i) {
+    const int k0 = chunk * kNormChunk + (w + 4 * i) * 32 + j * 8;
+    p[i] = 0.f;
     if (!live || k0 >= d) continue;
     float* x = X + (size_t)m * d + k0;
     const float* a = P + (size_t)m * d + k0;
+    float4 b[KS][2];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      b[q][0] = *(const float4*)(a + q * stride);
+      b[q][1] = *(const float4*)(a + q * stride + 4);
+    }
     float v[8];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      float4 u = *(float4*)(x + 4 * h);
-      const float4 b = *(const float4*)(a + 4 * h);
-      u.x = u.x + (0.f + b.x);
-      u.y = u.y + (0.f + b.y);
-      u.z = u.z + (0.f + b.z);
-      u.w = u.w + (0.f + b.w);
+      float4 u = *(float4*)(x + 4 * h), s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int q = 0; q < KS; ++q) {
+        s.x += b[q][h].x;
+        s.y += b[q][h].y;
+        s.z += b[q][h].z;
+        s.w += b[q][h].w;
+      }
+      u.x = u.x + s.x;
+      u.y = u.y + s.y;
+      u.z = u.z + s.z;
+      u.w = u.w + s.w;
       *(float4*)(x + 4 * h) = u;
-      if (Xcopy) *(float4*)(Xcopy + (size_t)m * d + k0 + 4 * h) = u;
+      if (Xcopy) *(float4*)(Xcopy + k0 + 4 * h) = u;
       v[4 * h + 0] = u.x;
       v[4 * h + 1] = u.y;
       v[4 * h + 2] = u.z;
@@ -186,19 +205,18 @@ __global__ __launch_bounds__(64) void resid_add_rows_kernel(float* X, const floa
     float sq = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) sq += v[e] * v[e];
-    p[st] = sq;
+    p[i] = sq;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = v[e] * to_f<uint16_t>(g[k0 + e]);
     put_afrag<true, NT>(Y, m, k0, v, d >> 5, MBn);
   }
-  // wave_sum over the one-row form's threads T = 4 s + j: lane xor 32, 16, 8
-  // and 4 pair steps s ^ 8, s ^ 4, s ^ 2, s ^ 1 (this thread), xor 2 and 1
-  // pair groups j ^ 2 and j ^ 1 (lanes t ^ 32 and t ^ 16)
-#pragma unroll
-  for (int o = kSteps / 2; o > 0; o >>= 1)
-#pragma unroll
-    for (int st = 0; st < o; ++st) p[st] = p[st] + p[st + o];
-  float sq = p[0];
+  // wave_sum over the one-row form's threads T = 4 s + j: lane xor 32 and 16
+  // pair steps s ^ 8 and s ^ 4 (this thread), xor 8 and 4 steps s ^ 2 and s ^ 1
+  // (other waves), xor 2 and 1 groups j ^ 2 and j ^ 1 (lanes t ^ 32 and t ^ 16)
+  part[w][t] = (p[0] + p[2]) + (p[1] + p[3]);
+  __syncthreads();
+  if (w != 0) return;
+  float sq = (part[0][t] + part[2][t]) + (part[1][t] + part[3][t]);
   sq += __shfl_xor(sq, 32, 64);
   sq += __shfl_xor(sq, 16, 64);
   if (j == 0 && live) ss[(size_t)chunk * ss_stride + m] = sq;
@@ -498,18 +516,25 @@ __global__ __launch_bounds__(128) void kv_move_kernel(T* pool, int nblk, int KVH
 
 }  // namespace
 
-void launch_resid_add(bool bf16, int terms, float* X, const float* P, int ksplit, int M, int d, const void* g,
-                      void* Y, int MBn, const RowInfo* rows, float* ss, int ss_stride, hipStream_t s, float* Xcopy,
-                      const void* E, const RowInfo* erows) {
+// Rows from which the residual update takes its many-row form.
+constexpr int kResidRowsMin = 128;
+
+void launch_resid_add(bool bf16, float* X, const float* P, int ksplit, int M, int d, const void* g, void* Y, int MBn,
+                      const RowInfo* rows, float* ss, int ss_stride, hipStream_t s, float* Xcopy, const void* E,
+                      const RowInfo* erows) {
   const dim3 grid((d + kNormChunk - 1) / kNormChunk, M);
-  if (bf16 && P && ksplit == 1 && !rows && !E && !erows && M > kPrefillMinRows && (terms == 2 || terms == 3)) {
+  if (bf16 && P && !rows && !E && M >= kResidRowsMin && (ksplit == 1 || ksplit == 2 || ksplit == 4 || ksplit == 8)) {
     const dim3 rgrid((d + kNormChunk - 1) / kNormChunk, (M + 15) / 16);
-    if (terms == 3)
-      hipLaunchKernelGGL(resid_add_rows_kernel<3>, rgrid, dim3(64), 0, s, X, P, M, d, (const uint16_t*)g, Y, MBn, ss,
-                         ss_stride, Xcopy);
-    else
-      hipLaunchKernelGGL(resid_add_rows_kernel<2>, rgrid, dim3(64), 0, s, X, P, M, d, (const uint16_t*)g, Y, MBn, ss,
-                         ss_stride, Xcopy);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, rgrid, dim3(256), 0, s, X, P, M, d, (const uint16_t*)g, Y, MBn, ss, ss_stride, Xcopy,
+                         erows);
+    };
+    switch (ksplit) {
+      case 1: go(resid_add_rows_kernel<kTerms, 1>); break;
+      case 2: go(resid_add_rows_kernel<kTerms, 2>); break;
+      case 4: go(resid_add_rows_kernel<kTerms, 4>); break;
+      default: go(resid_add_rows_kernel<kTerms, 8>); break;
+    }
     return;
   }
   if (!bf16) {
@@ -522,23 +547,17 @@ void launch_resid_add(bool bf16, int terms, float* X, const float* P, int ksplit
                        ss_stride, Xcopy, (const uint16_t*)E, erows);
   };
   // the split counts of the projections that feed it get their exact loads
-  if (terms >= 3) {
-    switch (P ? ksplit : 0) {
-      case 4: go(resid_add_kernel<uint16_t, true, 3, 4>); break;
-      case 8: go(resid_add_kernel<uint16_t, true, 3, 8>); break;
-      default: go(resid_add_kernel<uint16_t, true, 3, 0>); break;
-    }
-  } else {
-    switch (P ? ksplit : 0) {
-      case 4: go(resid_add_kernel<uint16_t, true, 2, 4>); break;
-      case 8: go(resid_add_kernel<uint16_t, true, 2, 8>); break;
-      default: go(resid_add_kernel<uint16_t, true, 2, 0>); break;
-    }
+  switch (P ? ksplit : 1) {
+    case 1: go(resid_add_kernel<uint16_t, true, kTerms, 1>); break;
+    case 2: go(resid_add_kernel<uint16_t, true, kTerms, 2>); break;
+    case 4: go(resid_add_kernel<uint16_t, true, kTerms, 4>); break;
+    case 8: go(resid_add_kernel<uint16_t, true, kTerms, 8>); break;
+    default: go(resid_add_kernel<uint16_t, true, kTerms, 0>); break;
   }
 }
 
 void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
-  if (a.M > kPrefillMinRows && a.hd <= 128) {  // many rows: angles shared per row
+  if (a.M > kManyRows && a.hd <= 128) {  // many rows: angles shared per row
     if (bf16)
       hipLaunchKernelGGL(qkv_finish_rows_kernel<uint16_t>, dim3(a.M), dim3(256), 0, s, a);
     else
@@ -552,6 +571,7 @@ void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
       case 1: go(qkv_finish_kernel<uint16_t, 1>); break;
       case 2: go(qkv_finish_kernel<uint16_t, 2>); break;
       case 4: go(qkv_finish_kernel<uint16_t, 4>); break;
+      case 8: go(qkv_finish_kernel<uint16_t, 8>); break;
       default: go(qkv_finish_kernel<uint16_t, 0>); break;
     }
   } else {

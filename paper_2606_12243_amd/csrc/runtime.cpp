@@ -26,11 +26,9 @@ size_t al(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 int esize_of(const via_model_desc* d) { return d->dtype == VIA_DTYPE_BF16 ? 2 : 4; }
 
-// Split-K policy: about two work-groups per CU, at least two 32-wide K steps
-// per wave (8 waves) in each slice.  Depends only on the GEMM shape.
-// K splits of a GEMM: as many work-groups as fit the 256 compute units in one
-// round (a GEMM work-group occupies a whole CU, so a 257th would run alone
-// in a second round), with at least 8 steps of 32 per split.
+// K splits of an fp32 model's GEMM: as many work-groups as fit the 256 compute
+// units in one round (a GEMM work-group occupies a whole CU, so a 257th would
+// run alone in a second round), with at least 8 steps of 32 per split.
 int choose_ksplit(int N, int K) {
   const int tiles = gemm_tiles(N);
   return std::max(1, std::min(256 / std::max(1, tiles), K / 256));
@@ -40,6 +38,16 @@ struct GemmShape {
   int N, K, ks;
   GemmRole role;
   int nb_ki, ks_ki;  // the K-interleaved kernel's blocks per work-group and splits (forwards of <= 32 rows)
+
+  // K splits of a forward of M rows
+  int splits(bool bf16, int M) const {
+    switch (gemm_path(bf16, role, M, N, K)) {
+      case GemmPath::kStaged: return ks;
+      case GemmPath::kStream: return ks_ki;
+      case GemmPath::kRowTile: return gemm_splits(role, M, N, K);
+      default: return 1;
+    }
+  }
 };
 
 struct Dims {
@@ -96,28 +104,31 @@ Layout layout_of(const via_model_desc* desc, int max_rows, int max_batch, int ma
   };
   const size_t R = max_rows;
   // activation fragments: rows padded to the GEMM row group; bf16 models
-  // keep kQkvTerms bf16 terms for the QKV input, 2 elsewhere; fp32 models 1 fp32
+  // keep kTerms bf16 terms per activation, fp32 models 1 fp32
   const size_t Rp = (size_t)gemm_padded_rows(max_rows);
-  const size_t fq = es == 2 ? 2 * std::max(2, kQkvTerms) : 4, f2 = 4;
+  const size_t fq = es == 2 ? 2 * kTerms : 4, f2 = 4;
   L.X = take(R * D.d * 4);
   L.Yf = take(Rp * D.d * fq);
   L.Q = take(R * D.H * D.hd * 4);
   L.Af = take(Rp * D.H * D.hd * f2);
   L.Hf = take(Rp * D.F * f2);
   L.Ylf = take(Rp * D.d * f2);
-  // split-K partials of forwards of up to kPrefillMinRows rows; longer
-  // (prefill-sized) forwards write one partial of all their rows.  The
-  // gate/up kernels write h directly and need none.
+  // split-K partials: the most any forward of up to max_rows rows writes.  The
+  // splits depend on the rows only through the row tiles, so the last row
+  // count of each tile count is enough.  The gate/up kernels write h directly
+  // and need none.
   size_t part = 0;
-  for (const GemmShape& g : {D.g_qkv, D.g_o, D.g_down}) {
-    part = std::max(part, (size_t)std::max(g.ks, g.ks_ki) * std::min<size_t>(R, kPrefillMinRows) * g.N * 4);
-    if (gemm_is_prefill(es == 2, (int)R)) part = std::max(part, R * g.N * 4);
-  }
+  for (const GemmShape& g : {D.g_qkv, D.g_o, D.g_down})
+    for (size_t M = 32;; M += 32) {
+      const size_t m = std::min(M, R);
+      part = std::max(part, (size_t)g.splits(es == 2, (int)m) * m * g.N * 4);
+      if (M >= R) break;
+    }
   L.part = take(part);
   L.max_chunks = std::min(kAttnMaxSplits, ceil_div(max_blocks * kBlock, 32));
   L.att_o = take((size_t)L.max_chunks * R * D.H * D.hd * 4);
   L.att_ml = take((size_t)L.max_chunks * R * D.H * 2 * 4);
-  L.lm_part = take((size_t)gemm_tiles(D.V) * R * 4 * 4);
+  L.lm_part = take((size_t)ceil_div(D.V, 128) * R * 4 * 4);  // column tiles of 128 or 256
   L.ss = take((size_t)ceil_div(D.d, kNormChunk) * R * 4);  // RMSNorm sums of squares [chunk][row]
   L.xstate = take((size_t)max_seqs * kStateRows * D.d * 4);
   L.max_items = ceil_div(max_rows * D.G, kAttnQueries) + max_batch;
@@ -347,10 +358,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
     route = m->route;
   const float eps = m->d.rms_eps;
 
-  // K splits of each projection's partials (one on the prefill GEMM)
-  const bool prefill_gemm = gemm_is_prefill(bf, M);
-  auto ki = [&](const GemmShape& sh) { return bf && gemm_uses_ki(sh.role, M, sh.N); };
-  auto ks = [&](const GemmShape& sh) { return prefill_gemm ? 1 : ki(sh) ? sh.ks_ki : sh.ks; };
+  auto ks = [&](const GemmShape& sh) { return sh.splits(bf, M); };
   auto gemm = [&](const void* Xf, const void* W, const GemmShape& sh, GemmRole role, int kind) {
     GemmArgs g{};
     g.X = Xf;
@@ -360,7 +368,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
     g.K = sh.K;
     g.N = sh.N;
     g.ksplit = ks(sh);
-    g.nb = ki(sh) ? sh.nb_ki : 0;
+    g.nb = sh.nb_ki;
     g.part = part;
     timed_gemm(kv, kind, bf, role, g, s);
   };
@@ -390,7 +398,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
     launch_prefix_copy(bf, pa, s);
   }
   // first layer's input norm; from layer 0 it also gathers the embedding rows into X
-  launch_resid_add(bf, kQkvTerms, X, nullptr, 1, M, D.d, m->attn_norm[route[start_si]], Yf, MBn, nullptr, ss, ss_stride, s,
+  launch_resid_add(bf, X, nullptr, 1, M, D.d, m->attn_norm[route[start_si]], Yf, MBn, nullptr, ss, ss_stride, s,
                    nullptr, start_si > 0 ? nullptr : m->embed, d_rows);
   at.q_hi = Q;
   at.q_lo = Qlo;
@@ -431,14 +439,13 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
   qa.eps = eps;
   for (size_t si = start_si; si < route.size(); ++si) {
     const int l = route[si];
-    // Q/K/V from kQkvTerms bf16 terms per activation (the K/V are rounded to the cache's bf16)
     gemm(Yf, m->w_qkv[l], D.g_qkv, GemmRole::kQkv, VIA_KERNEL_QKV);
     qa.layer_slot = (int)si;
     launch_qkv_finish(bf, qa, s);
     at.layer_slot = (int)si;
     timed_launch(kv, VIA_KERNEL_ATTN, s, [&] { launch_attention(bf, at, s); });
     gemm(Af, m->w_o[l], D.g_o, GemmRole::kO, VIA_KERNEL_O);
-    launch_resid_add(bf, 2, X, part, ks(D.g_o), M, D.d, m->ffn_norm[l], Yf, MBn, nullptr, ss, ss_stride, s);
+    launch_resid_add(bf, X, part, ks(D.g_o), M, D.d, m->ffn_norm[l], Yf, MBn, nullptr, ss, ss_stride, s);
     {
       GemmArgs g{};
       g.X = Yf;
@@ -465,7 +472,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
       float* xcopy = at_shared && save_prefix ? (float*)(ws + L.xstate)
                      : at_shared && save_rows ? (float*)(ws + L.Ylf)
                                               : nullptr;
-      launch_resid_add(bf, kQkvTerms, X, part, ks(D.g_down), M, D.d, m->attn_norm[route[si + 1]], Yf, MBn, nullptr, ss,
+      launch_resid_add(bf, X, part, ks(D.g_down), M, D.d, m->attn_norm[route[si + 1]], Yf, MBn, nullptr, ss,
                        ss_stride, s, xcopy, nullptr, save_rows ? nullptr : d_rows);
     }
   }
@@ -475,7 +482,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
     void* Ylf = ws + L.Ylf;
     const int MBl = gemm_padded_rows(nlm) / 16;
     // last residual update, final norm of the head rows only
-    launch_resid_add(bf, 2, X, part, ks(D.g_down), M, D.d, m->final_norm, Ylf, MBl, d_rows, ss, ss_stride, s);
+    launch_resid_add(bf, X, part, ks(D.g_down), M, D.d, m->final_norm, Ylf, MBl, d_rows, ss, ss_stride, s);
     GemmArgs h{};
     h.X = Ylf;
     h.MBn = MBl;
@@ -494,7 +501,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
     h.eps = eps;
     timed_launch(kv, VIA_KERNEL_HEAD, s, [&] {
       launch_gemm(bf, GemmRole::kHead, h, s);
-      launch_lm_finalize(d_lm, h.lm_part, nlm, gemm_tiles(D.V), inv_T, out->row_argmax, out->row_max,
+      launch_lm_finalize(d_lm, h.lm_part, nlm, gemm_head_tiles(bf, nlm, D.V, D.d), inv_T, out->row_argmax, out->row_max,
                          out->row_sumexp, out->row_gap, s);
     });
   }

@@ -1,0 +1,67 @@
+"""Forwards of 33 rows and more on the row-tile GEMM (tiles of 64, 96 or 128
+rows x 128 or 256 columns, 1 to 8 K splits) and the many-row residual update:
+probe forwards of a teacher-forced window against the oracle's fp64 logits.
+
+Row counts sit at the edges of the tiles (33, 64 | 65, 96 | 97, 128 | 129) and
+past them, where two or more row tiles and the 256-column tiles are taken; one
+model has ragged column tails (vocabulary 3001, FFN 1408) and no split, the
+other splits its K (2112 and 4160, whose last split is the shortest) 2 to 8
+ways.  Tolerance: the bf16 logit bound of the lock-step tests (2e-2), which
+covers the 2-term activations and the bf16 cache; logits here have a standard
+deviation of about 0.9.
+"""
+import ctypes as C
+import functools
+
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from oracle.model import OracleModel  # noqa: E402
+from paper_2606_12243_amd import via  # noqa: E402
+from workload import configs, gen  # noqa: E402
+
+SPLIT = dict(name="split_k", seed_w=21, seed_c=22, route=[0],
+             model=dict(n_layers=1, d_model=2112, n_heads=16, n_kv_heads=4, head_dim=128, d_ffn=4160, vocab=700,
+                        dtype="bf16", rms_eps=1e-5, rope_theta=10000.0))
+
+
+@functools.lru_cache(maxsize=None)
+def models(name):
+    cfg = SPLIT if name == "split_k" else dict(configs.get(name), seed_c=23)
+    W = gen.model_weights(cfg)
+    return cfg, via.Model(cfg["model"], W, list(range(cfg["model"]["n_layers"]))), OracleModel(cfg["model"], W)
+
+
+@pytest.mark.parametrize("name,rows", [(n, r) for n in ("small_bf16_hd128", "split_k")
+                                       for r in (33, 64, 65, 96, 97, 128, 129, 192, 193, 300, 520)])
+def test_window_logits_match_oracle(name, rows):
+    print(f"[case] row tile {name} rows={rows}", flush=True)
+    cfg, model, oracle = models(name)
+    V = cfg["model"]["vocab"]
+    tokens = gen.context_tokens(cfg, 0, rows)
+    blocks = (rows + via.BLOCK - 1) // via.BLOCK
+    kv = via.KV(model, max_seqs=1, max_blocks_per_seq=blocks, blocks_full=blocks, blocks_slim=blocks, max_rows=rows,
+                max_batch=1, max_drafts=1)
+    try:
+        via.check(via.via_kv_seq_reserve(kv.h, 0, 0))
+        out = via.Out(1, rows, 1, V, logits=True)
+        w = via.WindowBuf([0], [tokens], [[]], [[]], max_drafts=1)
+        p = via.tier_params(0.9, 0.5, 1.0)
+        via.check(via.via_verify_probe(model.h, kv.h, via.CACHE_FULL, C.byref(w.c), C.byref(p), C.byref(out.c),
+                                       via.stream_ptr()))
+        torch.cuda.synchronize()
+        got = out.logits.view(rows, V).cpu().double()
+        ref = oracle.forward_sequence(tokens)
+        assert (got - ref).abs().max().item() < 2e-2
+        # the row statistics are those of the logits written
+        assert torch.equal(out.row_argmax.cpu().long(), got.argmax(1))
+        assert torch.equal(out.row_max.cpu().double(), got.amax(1))
+        se = torch.exp(got - got.amax(1, keepdim=True)).sum(1)
+        assert ((out.row_sumexp.cpu().double() - se).abs() / se).max().item() < 1e-5
+    finally:
+        kv.close()
