@@ -403,47 +403,167 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnArgs a) {
   put_afrag<true, 2>(a.out, row, head * HD + d0, O, (a.H * HD) >> 5, a.MBn);
 }
 
-// fp32: one wave per (row, head); lane holds head_dim/64 dims.
+// fp32 models: a work-group of 256 threads takes one item (up to 32 queries)
+// and KV head, 256 keys at a time.  Scores: thread = key, 8 queries per pass
+// over its K row (16 tokens of a page are adjacent, so the loads coalesce);
+// online softmax: a wave per query; P V: thread = (dim, share of the pages),
+// accumulating every query in registers.  The serial form it replaces (a wave
+// per query walking the keys one by one, a cross-lane sum each) took 30 us at
+// 36 keys, latency all of it; this takes 5.
 template <int HD>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
-  constexpr int PER = HD / 64;
-  const int row = blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
-  const RowInfo ri = a.rows[row];
-  const SeqInfo si = a.seqs[ri.seq];
-  const int G = a.H / a.KVH, g = head / G;
-  const float* Q = (const float*)a.q_hi;
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
+  constexpr int kKeys = 256, kParts = 256 / HD, kQ = kAttnQueries;
+  const AttnItem it = a.items[blockIdx.x];
+  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int G = a.H / a.KVH;
+  const int nq = min(kQ, it.n_rows * G - it.q0);
   const float* pool = (const float*)a.pool;
-  float q[PER], acc[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    q[e] = Q[((size_t)row * a.H + head) * HD + lane * PER + e];
-    acc[e] = 0.f;
+  __shared__ __align__(16) float q_s[kQ][HD];
+  __shared__ __align__(16) float p_s[kQ][kKeys];
+  __shared__ float m_s[kQ], l_s[kQ], al_s[kQ];
+  __shared__ int vis_s[kQ];
+  __shared__ uint64_t mask_s[kQ];
+  for (int e = tid; e < nq * HD; e += 256) {
+    const int q = e / HD, i = e - q * HD, rl = (it.q0 + q) / G;
+    const int head = g * G + (it.q0 + q - rl * G);
+    q_s[q][i] = ((const float*)a.q_hi)[((size_t)(it.row_start + rl) * a.H + head) * HD + i];
   }
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int key = 0; key < si.kv_len; ++key) {
-    if (!key_visible(key, si.kv_len, ri, si.win_base)) continue;
-    int blk = a.btab[si.bt + key / kBlock], t = key % kBlock;
-    float dot = 0.f;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) dot += q[e] * pool[k_off(a.layer_slot, blk, a.pool_blocks, a.KVH, HD, g, t, lane * PER + e)];
-    float s = wave_sum(dot) * a.scale;
-    float m_new = fmaxf(m_run, s);
-    float alpha = expf(m_run - m_new), p = expf(s - m_new);
-    l_run = l_run * alpha + p;
-#pragma unroll
-    for (int e = 0; e < PER; ++e)
-      acc[e] = acc[e] * alpha + p * pool[v_off(a.layer_slot, blk, a.pool_blocks, a.KVH, HD, g, t, lane * PER + e)];
-    m_run = m_new;
+  if (tid < nq) {
+    const RowInfo ri = a.rows[it.row_start + (it.q0 + tid) / G];
+    vis_s[tid] = ri.vis_len;
+    mask_s[tid] = ri.mask;
+    m_s[tid] = -INFINITY;
+    l_s[tid] = 0.f;
   }
-  __shared__ float o_s[HD];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) o_s[lane * PER + e] = acc[e] / l_run;
   __syncthreads();
-  if (lane < HD / 8) {
+  int min_vis = it.kv_len;
+  for (int q = 0; q < nq; ++q) min_vis = min(min_vis, vis_s[q]);
+  const int d = tid % HD, part = tid / HD;
+  float o[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) o[q] = 0.f;
+  for (int kb = 0; kb < it.kv_len; kb += kKeys) {
+    const bool all_visible = kb + kKeys <= min_vis;  // uniform
+    {
+      const int key = min(kb + tid, it.kv_len - 1);  // past the end: the last key again, masked below
+      const float* kp = pool + k_off(a.layer_slot, a.btab[it.bt + key / kBlock], a.pool_blocks, a.KVH, HD, g, key % kBlock, 0);
+      for (int q0 = 0; q0 < nq; q0 += 8) {
+        float s[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s[q] = 0.f;
+#pragma unroll 4
+        for (int dg = 0; dg < HD / 8; ++dg) {
+          const float4 k0 = *(const float4*)(kp + dg * kBlock * 8), k1 = *(const float4*)(kp + dg * kBlock * 8 + 4);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const float4 x0 = *(const float4*)&q_s[q0 + q][dg * 8], x1 = *(const float4*)&q_s[q0 + q][dg * 8 + 4];
+            float t = s[q];
+            t = fmaf(x0.x, k0.x, t);
+            t = fmaf(x0.y, k0.y, t);
+            t = fmaf(x0.z, k0.z, t);
+            t = fmaf(x0.w, k0.w, t);
+            t = fmaf(x1.x, k1.x, t);
+            t = fmaf(x1.y, k1.y, t);
+            t = fmaf(x1.z, k1.z, t);
+            s[q] = fmaf(x1.w, k1.w, t);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (q0 + q < nq) {
+            RowInfo ri;
+            ri.vis_len = vis_s[q0 + q];
+            ri.mask = mask_s[q0 + q];
+            p_s[q0 + q][tid] = key_visible(kb + tid, it.kv_len, ri, it.win_base) ? s[q] * a.scale : -INFINITY;
+          }
+      }
+    }
+    __syncthreads();
+    for (int q = wave; q < nq; q += 4) {
+      float v[kKeys / 64], mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < kKeys / 64; ++i) {
+        v[i] = p_s[q][i * 64 + lane];
+        mx = fmaxf(mx, v[i]);
+      }
+      const float m_old = m_s[q], m_new = fmaxf(m_old, wave_max(mx));
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < kKeys / 64; ++i) {
+        const float p = v[i] == -INFINITY ? 0.f : expf(v[i] - m_new);  // NaN scores stay NaN
+        p_s[q][i * 64 + lane] = p;
+        sum += p;
+      }
+      sum = wave_sum(sum);
+      if (lane == 0) {
+        const float al = m_old == -INFINITY ? 0.f : expf(m_old - m_new);
+        al_s[q] = al;
+        l_s[q] = l_s[q] * al + sum;
+        m_s[q] = m_new;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+      if (q < nq) o[q] *= al_s[q];
+    const int np = (min(kKeys, it.kv_len - kb) + kBlock - 1) / kBlock;
+    for (int p = part; p < np; p += kParts) {
+      const float* vp = pool + v_off(a.layer_slot, a.btab[it.bt + kb / kBlock + p], a.pool_blocks, a.KVH, HD, g, 0, d);
+      float v[kBlock];
+#pragma unroll
+      for (int t = 0; t < kBlock; t += 4) *(float4*)&v[t] = *(const float4*)(vp + t);
+      if (all_visible) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+          if (q < nq)
+#pragma unroll
+            for (int t = 0; t < kBlock; t += 4) {
+              const float4 w = *(const float4*)&p_s[q][p * kBlock + t];
+              o[q] = fmaf(w.x, v[t], o[q]);
+              o[q] = fmaf(w.y, v[t + 1], o[q]);
+              o[q] = fmaf(w.z, v[t + 2], o[q]);
+              o[q] = fmaf(w.w, v[t + 3], o[q]);
+            }
+      } else {
+        // a key a query does not see adds nothing, whatever its page holds
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+          if (q < nq)
+#pragma unroll
+            for (int t = 0; t < kBlock; ++t) {
+              const float w = p_s[q][p * kBlock + t];
+              o[q] = w == 0.f ? o[q] : fmaf(w, v[t], o[q]);
+            }
+      }
+    }
+    __syncthreads();  // the scores' buffer is free again
+  }
+  // sum of the page shares (in order), scaled by 1 / l, through the scores' buffer
+  float* r_s = &p_s[0][0];  // [part][q][HD] would exceed it at 32 queries: one share at a time
+  for (int s = 1; s < kParts; ++s) {
+    if (part == s)
+#pragma unroll
+      for (int q = 0; q < kQ; ++q)
+        if (q < nq) r_s[q * HD + d] = o[q];
+    __syncthreads();
+    if (part == 0)
+#pragma unroll
+      for (int q = 0; q < kQ; ++q)
+        if (q < nq) o[q] += r_s[q * HD + d];
+    __syncthreads();
+  }
+  if (part == 0)
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+      if (q < nq) r_s[q * HD + d] = o[q] / l_s[q];
+  __syncthreads();
+  for (int e = tid; e < nq * (HD / 8); e += 256) {
+    const int q = e / (HD / 8), i = e - q * (HD / 8), rl = (it.q0 + q) / G;
+    const int head = g * G + (it.q0 + q - rl * G);
     float v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = o_s[lane * 8 + e];
-    put_afrag<false, 1>(a.out, row, head * HD + lane * 8, v, (a.H * HD) >> 5, a.MBn);
+    for (int c = 0; c < 8; ++c) v[c] = r_s[q * HD + i * 8 + c];
+    put_afrag<false, 1>(a.out, it.row_start + rl, head * HD + i * 8, v, (a.H * HD) >> 5, a.MBn);
   }
 }
 
@@ -464,11 +584,11 @@ void launch_attention(bool bf16, const AttnArgs& a, hipStream_t s) {
         hipLaunchKernelGGL(attn_combine_kernel<64>, dim3(a.n_items * (kAttnQueries / 16), a.KVH), dim3(128), 0, s, b);
     }
   } else {
-    dim3 grid(a.M, a.H);
+    dim3 grid(a.n_items, a.KVH);
     if (a.hd == 128)
-      hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64), 0, s, a);
+      hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, a);
     else
-      hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64), 0, s, a);
+      hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, a);
   }
 }
 

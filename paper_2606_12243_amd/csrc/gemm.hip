@@ -1,15 +1,15 @@
 // GEMMs of the verification forward: P[split][M][N] = X[M, K-slice] * W[N,
 // K-slice]^T with M = fed rows and W packed.  gemm_path picks the kernel family
-// by the number of rows: weights streamed past registers (up to 32 rows), LDS-fed
-// row tiles, 256 x 256 prefill tiles; fp32 models and the bf16 head of up to 32
-// rows run the LDS-staged kernels.
+// by the number of rows: weights streamed past registers (up to 32 rows, with
+// an LDS-staged kernel for the head), LDS-fed row tiles, 256 x 256 prefill
+// tiles; fp32 models have one kernel of their own.
 //
-// LDS-staged kernels: a work-group of 8 waves owns a 256-column tile, one row
-// group and one K slice; each wave owns two 16-column blocks and streams their
-// weights over the whole slice, two chunks of steps ahead of its multiply.  The
-// activation fragments (X) of a chunk are loaded once per work-group into LDS
-// (double-buffered) and read there by all eight waves, so X leaves L2 once per
-// work-group and no cross-wave reduction is needed.
+// LDS-staged head: a work-group of 8 waves owns a 256-column tile; each wave
+// owns two 16-column blocks and streams their weights over all of K, two
+// chunks of steps ahead of its multiply.  The activation fragments (X) of a
+// chunk are loaded once per work-group into LDS (double-buffered) and read
+// there by all eight waves, so X leaves L2 once per work-group and no
+// cross-wave reduction is needed.
 //
 // The K slices of a tile ("splits") are written as separate fp32 partial tiles
 // and summed, in split order, by the consumer kernel after the kernel boundary:
@@ -26,7 +26,7 @@
 // significant bits).  Output register r of lane l is row (l/16)*4 + r, column
 // l%16.  The head reduces its tile to per-row (max, second, sum-exp, argmax)
 // partials and draft-token logits in place.
-// fp32 path: plain FMA on the vector ALUs (small models only).
+// fp32 models multiply in fp32 (v_mfma_f32_16x16x4_f32).
 #include <hip/hip_ext.h>
 
 #include "kernels.h"
@@ -39,6 +39,7 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 constexpr int kNBW = 2;                // 16-column blocks per wave
 constexpr int kTileN = 8 * 16 * kNBW;   // columns per work-group tile (8 waves)
+int gemm_tiles(int N) { return (N + kTileN - 1) / kTileN; }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -188,68 +189,6 @@ __device__ void tile_bf16(const GemmArgs& a, int c0, int m0, int st_beg, int st_
 #undef TILE_LOAD_W
 }
 
-// fp32 tile on the vector ALUs (X fragments with one fp32 term): rows
-// m0 .. m0+16*MB, columns c0 .. c0+ncols (ncols <= kTileN), K range
-// [k_beg, k_end), written to lds[r * ldc + c].  Thread t owns column
-// t % kTileN and every other 8-wide K group (t / kTileN selects which); the
-// 8 consecutive weights of a column and K group are 32 contiguous bytes of
-// the packed layout (two float4 loads), used for the 16 rows of a row block
-// (row blocks run one after another, so 16 accumulators suffice).  The two
-// halves are added in LDS, half 0 + half 1, so the order is fixed.
-template <int MB>
-__device__ void tile_f32(const GemmArgs& a, int c0, int m0, int k_beg, int k_end, float* lds, int ncols = kTileN,
-                         int ldc = kTileN) {
-  static_assert(kThreads == 2 * kTileN, "two threads per column");
-  const float4* W = (const float4*)a.W;
-  const float4* X = (const float4*)a.X;
-  const int steps = a.K >> 5;
-  const int c = threadIdx.x % kTileN, part = threadIdx.x / kTileN;
-  const int col = c0 + c;
-  const bool live = c < ncols && col < a.N;
-  // group of (col, k) in the packed layout: wbase + (k/32) * 256 + ((k%32)/8) * 16
-  const size_t wbase = (size_t)(col >> 6) * steps * 256 + ((col & 63) >> 4) * 64 + (col & 15);
-#pragma unroll 1
-  for (int mb = 0; mb < MB; ++mb) {
-    const int r0 = m0 + mb * 16;
-    if (r0 >= a.M) break;  // uniform
-    const int nr = min(16, a.M - r0);
-    float acc[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    if (live) {
-      for (int kg = (k_beg >> 3) + part; kg < (k_end >> 3); kg += 2) {
-        const size_t wg = wbase + (size_t)(kg >> 2) * 256 + (kg & 3) * 16;
-        const float4 w0 = W[wg * 2], w1 = W[wg * 2 + 1];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if (r >= nr) break;  // uniform
-          const size_t xg = afrag_group(0, r0 + r, kg * 8, steps, a.MBn);
-          const float4 x0 = X[xg * 2], x1 = X[xg * 2 + 1];
-          float t = acc[r];
-          t = fmaf(x0.x, w0.x, t);
-          t = fmaf(x0.y, w0.y, t);
-          t = fmaf(x0.z, w0.z, t);
-          t = fmaf(x0.w, w0.w, t);
-          t = fmaf(x1.x, w1.x, t);
-          t = fmaf(x1.y, w1.y, t);
-          t = fmaf(x1.z, w1.z, t);
-          t = fmaf(x1.w, w1.w, t);
-          acc[r] = t;
-        }
-      }
-    }
-    float* o = lds + (size_t)mb * 16 * ldc + c;
-    if (part == 1 && c < ncols)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[r * ldc] = acc[r];
-    __syncthreads();
-    if (part == 0 && c < ncols)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[r * ldc] = acc[r] + o[r * ldc];
-    __syncthreads();
-  }
-}
-
 // (max, argmax, second) merge with lowest-index tie break
 __device__ __forceinline__ void merge3(float& mx, int& am, float& sc, float mx2, int am2, float sc2) {
   if (mx2 > mx || (mx2 == mx && am2 < am)) {
@@ -306,122 +245,154 @@ __device__ void epi_stats(const GemmArgs& a, int tile, int m0, const float* lds)
   }
 }
 
-template <typename T, int MB, int NT, int NBW, int C, bool STATS>
-__device__ __forceinline__ void gemm_body(const GemmArgs& a) {
-  using TS = TileShape<MB, NT, NBW, C>;
-  static_assert(TS::kCols == kTileN, "tile width");
+// Head of up to 32 rows (bf16): tiles of 256 columns over all of K.
+template <int MB, int C>
+__global__ __launch_bounds__(kThreads) void gemm_head(GemmArgs a) {
+  using TS = TileShape<MB, kTerms, kNBW, C>;
   constexpr int kLdsX = 2 * TS::kXChunk * 16;               // bytes of the X double buffer
   constexpr int kLdsT = 16 * MB * kTileN * 4;                // bytes of an fp32 output tile
-  constexpr int kLds = (sizeof(T) == 2 ? kLdsX : 0) > kLdsT ? (sizeof(T) == 2 ? kLdsX : 0) : kLdsT;
+  constexpr int kLds = kLdsX > kLdsT ? kLdsX : kLdsT;
   __shared__ __align__(16) unsigned char smem[kLds];
   float* lds = (float*)smem;
-  // block -> (tile, split, m-group), m-group fastest
-  const int mgroups = (a.M + 16 * MB - 1) / (16 * MB);
-  int b = blockIdx.x;
-  const int mg = b % mgroups;
-  b /= mgroups;
-  const int split = b % a.ksplit;
-  const int tile = b / a.ksplit;
-  const int m0 = mg * 16 * MB, c0 = tile * kTileN;
-  const int steps = a.K >> 5, per = (steps + a.ksplit - 1) / a.ksplit;
-  const int st_beg = min(steps, split * per), st_end = min(steps, (split + 1) * per);
-  if constexpr (sizeof(T) == 2 && MB % 2 == 0 && NBW == 2) {
+  const int tile = blockIdx.x, c0 = tile * kTileN, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if constexpr (MB % 2 == 0) {
     // 32x32x16 MFMAs: tile i, register r of lane l is row 32i + (r/4)*8 + (l/32)*4 + r%4,
     // column wave*32 + l%32 of the work-group's tile
     f32x16 acc[MB / 2];
-    tile_bf16<MB, NT, NBW, C, true>(a, c0, m0, st_beg, st_end, (uint4*)smem, acc);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    tile_bf16<MB, kTerms, kNBW, C, true>(a, c0, 0, 0, a.K >> 5, (uint4*)smem, acc);
     const int cl = wave * 32 + (lane & 31), rl = (lane >> 5) * 4;
-    if constexpr (STATS) {
-      __syncthreads();  // the X buffers become the output tile
+    __syncthreads();  // the X buffers become the output tile
 #pragma unroll
-      for (int i = 0; i < MB / 2; ++i)
+    for (int i = 0; i < MB / 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) lds[(i * 32 + (r >> 2) * 8 + rl + (r & 3)) * kTileN + cl] = acc[i][r];
-      __syncthreads();
-      epi_stats<MB>(a, tile, m0, lds);
-    } else {
-      float* P = a.part + (size_t)split * a.M * a.N;
-      const int col = c0 + cl;
-#pragma unroll
-      for (int i = 0; i < MB / 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = m0 + i * 32 + (r >> 2) * 8 + rl + (r & 3);
-          if (m < a.M && col < a.N) P[(size_t)m * a.N + col] = acc[i][r];
-        }
-    }
-  } else if constexpr (sizeof(T) == 2) {
-    f32x4 acc[NBW][MB];
-    tile_bf16<MB, NT, NBW, C>(a, c0, m0, st_beg, st_end, (uint4*)smem, acc);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
-    if constexpr (STATS) {
-      __syncthreads();  // the X buffers become the output tile
-#pragma unroll
-      for (int j = 0; j < NBW; ++j)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) lds[(mb * 16 + g * 4 + r) * kTileN + (wave * NBW + j) * 16 + n] = acc[j][mb][r];
-      __syncthreads();
-      epi_stats<MB>(a, tile, m0, lds);
-    } else {
-      float* P = a.part + (size_t)split * a.M * a.N;
-#pragma unroll
-      for (int j = 0; j < NBW; ++j) {
-        const int col = c0 + (wave * NBW + j) * 16 + n;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = m0 + mb * 16 + g * 4 + r;
-            if (m < a.M && col < a.N) P[(size_t)m * a.N + col] = acc[j][mb][r];
-          }
-      }
-    }
+      for (int r = 0; r < 16; ++r) lds[(i * 32 + (r >> 2) * 8 + rl + (r & 3)) * kTileN + cl] = acc[i][r];
   } else {
-    tile_f32<MB>(a, c0, m0, st_beg * 32, st_end * 32, lds);
-    if constexpr (STATS) {
-      epi_stats<MB>(a, tile, m0, lds);
-    } else {
-      float* P = a.part + (size_t)split * a.M * a.N;
-      for (int e = threadIdx.x; e < 16 * MB * kTileN; e += kThreads) {
-        const int r = e / kTileN, c = e - r * kTileN, m = m0 + r, col = c0 + c;
-        if (m < a.M && col < a.N) P[(size_t)m * a.N + col] = lds[e];
-      }
-    }
+    f32x4 acc[kNBW][MB];
+    tile_bf16<MB, kTerms, kNBW, C>(a, c0, 0, 0, a.K >> 5, (uint4*)smem, acc);
+    const int n = lane & 15, g = lane >> 4;
+    __syncthreads();  // the X buffers become the output tile
+#pragma unroll
+    for (int j = 0; j < kNBW; ++j)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) lds[(mb * 16 + g * 4 + r) * kTileN + (wave * kNBW + j) * 16 + n] = acc[j][mb][r];
   }
+  __syncthreads();
+  epi_stats<MB>(a, tile, 0, lds);
 }
 
-// Gate/up projection with SwiGLU, h = silu(x W_g) * (x W_u) (the verifier's
-// FFN), fp32 models.  The packed weight interleaves gate and up rows by 8
-// (launch_pack with ffn), so 16-column block b holds gate and up columns of
-// f = 8b .. 8b+7.  A work-group owns a.nb consecutive blocks over all of K, so
-// no partial sums leave it: the tile goes to LDS and the epilogue writes h for
-// its (row, 8-f group)s, the down projection's input.
-template <int MB>
-__global__ __launch_bounds__(kThreads) void gemm_gate_up(GemmArgs a) {
-  constexpr int kCols = kWaves * 16;                        // widest tile (nb = 8)
-  __shared__ __align__(16) float lds[16 * MB * kCols];
-  const int nblocks = a.N >> 4;             // 16-column blocks (= F / 8 groups of h)
-  const int blk0 = blockIdx.x * a.nb;
-  const int m0 = blockIdx.y * 16 * MB;
-  const int ncol = min(a.nb, nblocks - blk0) * 16;  // columns of this work-group
-  tile_f32<MB>(a, blk0 * 16, m0, 0, a.K, lds, ncol, kCols);
-  __syncthreads();
-  const int ngroups = ncol >> 4;
-  for (int e = threadIdx.x; e < 16 * MB * ngroups; e += kThreads) {
-    const int r = e / ngroups, j = e - r * ngroups, m = m0 + r;
-    if (m >= a.M) continue;
-    const float* t = lds + r * kCols + j * 16;
-    const float sc = row_scale(a.ss, a.ss_stride, m, a.K, a.eps);  // RMSNorm of the input row
-    float v[8];
+// Every projection of fp32 models, on v_mfma_f32_16x16x4_f32 (fp32 products
+// and sums).  The packed layouts give lane l of a 16-row (column) block the 8
+// consecutive k's (l/16)*8 .. +7 of each 32-wide step, so element e of all
+// lanes is one MFMA operand over the k's {e, 8 + e, 16 + e, 24 + e}.  These
+// models are small, so latency is the cost: a work-group owns NB column blocks
+// of 16 MB rows over all of K, its 8 waves interleave the K steps (one step of
+// loads ahead) and their partial tiles are added in LDS in wave order.  A K of
+// 256 is one step per wave: 14 us for the serial vector-ALU loop, now 4.
+enum class Epi { kPart, kSwiglu, kStats };  // what is done with a tile
+template <int MB, int NB, Epi EPI>
+__global__ __launch_bounds__(kThreads) void gemm_f32(GemmArgs a) {
+  constexpr int kCols = NB * 16, kStride = kCols + 4;
+  __shared__ __align__(16) float red[kWaves][16 * MB][kStride];
+  const int blk0 = blockIdx.x * NB, m0 = blockIdx.y * 16 * MB;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int S = a.K >> 5, t64 = (a.N + 63) >> 6;
+  const float4* wt[NB];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float gt = t[i] * sc, up = t[8 + i] * sc;
-      v[i] = gt / (1.0f + expf(-gt)) * up;
+  for (int j = 0; j < NB; ++j) {
+    const int blk = min(blk0 + j, t64 * 4 - 1);  // columns past N: never stored
+    wt[j] = (const float4*)a.W + ((size_t)(blk >> 2) * S * 256 + (blk & 3) * 64 + lane) * 2;
+  }
+  const float4* xt[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+    xt[i] = (const float4*)a.X + ((size_t)min((m0 >> 4) + i, a.MBn - 1) * 64 + lane) * 2;
+  f32x4 acc[NB][MB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < MB; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nst = max(0, (S - wave + kWaves - 1) / kWaves);  // steps of this wave
+  float4 w[2][NB][2], x[2][MB][2];
+  auto load = [&](int buf, int i) {
+    const size_t st = (size_t)(wave + min(i, nst - 1) * kWaves);
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) w[buf][j][h] = wt[j][st * 512 + h];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) x[buf][m][h] = xt[m][st * a.MBn * 128 + h];
+  };
+  auto compute = [&](int buf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+          const float4 xv = x[buf][m][h], wv = w[buf][j][h];
+          acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.x, wv.x, acc[j][m], 0, 0, 0);
+          acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.y, wv.y, acc[j][m], 0, 0, 0);
+          acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.z, wv.z, acc[j][m], 0, 0, 0);
+          acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.w, wv.w, acc[j][m], 0, 0, 0);
+        }
+  };
+  if (nst > 0) {
+    load(0, 0);
+    for (int i = 0; i < nst; i += 2) {
+      load(1, i + 1);
+      compute(0);
+      if (i + 1 >= nst) break;
+      load(0, i + 2);
+      compute(1);
     }
-    put_afrag<false, 1>(a.H, m, (blk0 + j) * 8, v, a.F >> 5, a.MBn);
+  }
+  const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][i * 16 + g * 4 + r][j * 16 + n] = acc[j][i][r];
+  __syncthreads();
+  if constexpr (EPI == Epi::kSwiglu) {
+    for (int e = threadIdx.x; e < 16 * MB * NB; e += kThreads) {
+      const int r = e / NB, j = e - r * NB, m = m0 + r;
+      if (m >= a.M || blk0 + j >= a.N >> 4) continue;
+      const float sc = row_scale(a.ss, a.ss_stride, m, a.K, a.eps);  // RMSNorm of the input row
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float gt = 0.f, up = 0.f;
+#pragma unroll
+        for (int wv = 0; wv < kWaves; ++wv) {
+          gt += red[wv][r][j * 16 + i];
+          up += red[wv][r][j * 16 + 8 + i];
+        }
+        gt *= sc;
+        up *= sc;
+        v[i] = gt / (1.0f + expf(-gt)) * up;
+      }
+      put_afrag<false, 1>(a.H, m, (blk0 + j) * 8, v, a.F >> 5, a.MBn);
+    }
+  } else {
+    for (int e = threadIdx.x; e < 16 * MB * kCols; e += kThreads) {
+      const int r = e / kCols, c = e - r * kCols, m = m0 + r, col = blk0 * 16 + c;
+      float v = 0.f;
+#pragma unroll
+      for (int wv = 0; wv < kWaves; ++wv) v += red[wv][r][c];
+      if constexpr (EPI == Epi::kStats)
+        red[0][r][c] = v;
+      else if (m < a.M && col < a.N)
+        a.part[(size_t)m * a.N + col] = v;
+    }
+    if constexpr (EPI == Epi::kStats) {
+      __syncthreads();
+      epi_stats<MB, kCols, kStride>(a, blockIdx.x, m0, &red[0][0][0]);
+    }
   }
 }
 
@@ -527,23 +498,6 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up_ki(GemmArgs a) {
   }
 }
 
-// One entry point per projection, so kernel traces name the projection.
-#define VIA_GEMM_ENTRY(NAME, STATS)                                                       \
-  template <typename T, int MB, int C>                                                   \
-  __global__ __launch_bounds__(kThreads) void NAME(GemmArgs a) {                         \
-    gemm_body<T, MB, (sizeof(T) == 2 ? kTerms : 1), kNBW, C, STATS>(a);                  \
-  }
-VIA_GEMM_ENTRY(gemm_qkv, false)
-VIA_GEMM_ENTRY(gemm_o, false)
-VIA_GEMM_ENTRY(gemm_down, false)
-VIA_GEMM_ENTRY(gemm_head, true)
-#undef VIA_GEMM_ENTRY
-
-// X chunk steps: the chunk splits evenly over the threads (C * NT * MB a multiple of 8).
-template <typename T>
-constexpr int chunk_steps() {
-  return sizeof(T) == 2 ? 4 : 8;
-}
 // With timing events the launch carries them in its dispatch, so they
 // bracket the kernel itself rather than the stream around it.
 template <typename K>
@@ -553,44 +507,12 @@ void launch_timed(K kernel, dim3 grid, int threads, const GemmArgs& a, hipStream
   else
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a);
 }
-// bf16 models run only the head of up to 32 rows here (the other projections
-// and sizes have their own kernels); fp32 models run everything.
-#define VIA_GEMM_LAUNCH(NAME)                                                                     \
-  template <typename T>                                                                           \
-  void launch_##NAME(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {            \
-    const int mb = gemm_rows_per_group(a.M) / 16;                                                 \
-    const int mgroups = (a.M + 16 * mb - 1) / (16 * mb);                                          \
-    const dim3 grid(gemm_tiles(a.N) * a.ksplit * mgroups);                                        \
-    constexpr int C = chunk_steps<T>();                                                           \
-    auto go = [&](auto kernel) { launch_timed(kernel, grid, kThreads, a, s, e0, e1); };           \
-    if (mb == 1) return go(NAME<T, 1, C>);                                                        \
-    if (mb == 2) return go(NAME<T, 2, C>);                                                        \
-    if constexpr (sizeof(T) == 4) {                                                               \
-      if (mb == 3) return go(NAME<T, 3, C>);                                                      \
-      if (mb == 4) return go(NAME<T, 4, C>);                                                      \
-      if (mb == 6) return go(NAME<T, 6, C>);                                                      \
-      go(NAME<T, 8, C>);                                                                          \
-    }                                                                                             \
-  }
-VIA_GEMM_LAUNCH(gemm_qkv)
-VIA_GEMM_LAUNCH(gemm_o)
-VIA_GEMM_LAUNCH(gemm_down)
-VIA_GEMM_LAUNCH(gemm_head)
-#undef VIA_GEMM_LAUNCH
-
-// Gate/up with SwiGLU: grid (work-groups of a.nb blocks, row groups).
-void launch_gate_up_f32(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const int mb = gemm_rows_per_group(a.M) / 16;
-  const dim3 grid(((a.N >> 4) + a.nb - 1) / a.nb, (a.M + 16 * mb - 1) / (16 * mb));
-  auto go = [&](auto kernel) { launch_timed(kernel, grid, kThreads, a, s, e0, e1); };
-  switch (mb) {
-    case 1: go(gemm_gate_up<1>); break;
-    case 2: go(gemm_gate_up<2>); break;
-    case 3: go(gemm_gate_up<3>); break;
-    case 4: go(gemm_gate_up<4>); break;
-    case 6: go(gemm_gate_up<6>); break;
-    default: go(gemm_gate_up<8>); break;
-  }
+void launch_head(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(gemm_tiles(a.N));
+  if (a.M <= 16)
+    launch_timed(gemm_head<1, 4>, grid, kThreads, a, s, e0, e1);
+  else
+    launch_timed(gemm_head<2, 4>, grid, kThreads, a, s, e0, e1);
 }
 void launch_gate_up_ki(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid(((a.N >> 4) + a.nb - 1) / a.nb);
@@ -599,14 +521,20 @@ void launch_gate_up_ki(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
   else
     launch_timed(gemm_gate_up_ki<2>, grid, kThreads, a, s, e0, e1);
 }
-void launch_staged_f32(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (role) {
-    case GemmRole::kQkv: launch_gemm_qkv<float>(a, s, e0, e1); break;
-    case GemmRole::kO: launch_gemm_o<float>(a, s, e0, e1); break;
-    case GemmRole::kGateUp: launch_gate_up_f32(a, s, e0, e1); break;
-    case GemmRole::kDown: launch_gemm_down<float>(a, s, e0, e1); break;
-    case GemmRole::kHead: launch_gemm_head<float>(a, s, e0, e1); break;
-  }
+constexpr int kF32HeadCols = 64;  // columns of an fp32 head tile
+void launch_f32(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  // one 16-row block as far as it goes, else 64 rows; one column block per
+  // work-group until there are 256 of them with four
+  const int rows = a.M <= 16 ? 16 : 64, groups = (a.M + rows - 1) / rows;
+  const bool wide = role == GemmRole::kHead || (rows == 64 && (a.N + 63) / 64 * groups >= 256);
+  const dim3 grid(wide ? (a.N + 63) / 64 : (a.N + 15) / 16, groups);
+  auto go = [&](auto kernel) { launch_timed(kernel, grid, kThreads, a, s, e0, e1); };
+  if (role == GemmRole::kHead)
+    rows == 16 ? go(gemm_f32<1, 4, Epi::kStats>) : go(gemm_f32<4, 4, Epi::kStats>);
+  else if (role == GemmRole::kGateUp)
+    rows == 16 ? go(gemm_f32<1, 1, Epi::kSwiglu>) : wide ? go(gemm_f32<4, 4, Epi::kSwiglu>) : go(gemm_f32<4, 1, Epi::kSwiglu>);
+  else
+    rows == 16 ? go(gemm_f32<1, 1, Epi::kPart>) : wide ? go(gemm_f32<4, 4, Epi::kPart>) : go(gemm_f32<4, 1, Epi::kPart>);
 }
 
 
@@ -1106,7 +1034,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_prefill(GemmArgs a, int nt) 
 //
 // kPart writes one fp32 partial per split, kSwiglu (the gate/up projection)
 // writes h as in gemm_gate_up, kStats the head's row statistics.
-enum class RtEpi { kPart, kSwiglu, kStats };
 // Tile and K splits of one projection.
 struct RtPlan {
   int rows, cols, ks;
@@ -1150,7 +1077,7 @@ struct RtShape {
   static_assert(MB % 2 == 0 && (2 * MB) % WN == 0 && (WN == 2 || WN == 4), "wave split");
 };
 
-template <int MB, int WN, int KG, int SX, int SW, RtEpi EPI>
+template <int MB, int WN, int KG, int SX, int SW, Epi EPI>
 __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
   using SH = RtShape<MB, WN, KG, SX, SW>;
   constexpr int HB = MB / 2;  // row blocks of a wave
@@ -1291,7 +1218,7 @@ __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
   __builtin_amdgcn_s_waitcnt(0);  // the trailing copies land before LDS is reused or the work-group ends
   const int n = lane & 15, g = lane >> 4;
   float* tl = (float*)smem;
-  if constexpr (EPI == RtEpi::kPart && KG == 1) {
+  if constexpr (EPI == Epi::kPart && KG == 1) {
     float* P = a.part + (size_t)split * a.M * a.N;
 #pragma unroll
     for (int i = 0; i < HB; ++i)
@@ -1330,7 +1257,7 @@ __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
     }
     __syncthreads();
   }
-  if constexpr (EPI == RtEpi::kPart) {
+  if constexpr (EPI == Epi::kPart) {
     float* P = a.part + (size_t)split * a.M * a.N;
     const int c = threadIdx.x % (kBN / 4) * 4;
     for (int r = threadIdx.x / (kBN / 4); r < 16 * MB; r += kThr / (kBN / 4)) {
@@ -1338,7 +1265,7 @@ __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
       if (m >= a.M) break;
       if (col < a.N) *(float4*)(P + (size_t)m * a.N + col) = *(const float4*)(tl + r * kStride + c);  // N % 4 == 0
     }
-  } else if constexpr (EPI == RtEpi::kSwiglu) {
+  } else if constexpr (EPI == Epi::kSwiglu) {
     for (int e = threadIdx.x; e < 16 * MB * (kBN / 16); e += kThr) {
       const int r = e % (16 * MB), j = e / (16 * MB), m = m0 + r, f = (n0 >> 1) + j * 8;
       if (m >= a.M || f >= a.F) continue;
@@ -1365,8 +1292,8 @@ void launch_row_tile(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t
     launch_timed(role == GemmRole::kGateUp ? swiglu : role == GemmRole::kHead ? stats : part, grid, 512, a, s, e0, e1);
   };
 #define VIA_RT_PICK(...)                                                                        \
-  pick(gemm_row_tile<__VA_ARGS__, RtEpi::kPart>, gemm_row_tile<__VA_ARGS__, RtEpi::kSwiglu>,   \
-       gemm_row_tile<__VA_ARGS__, RtEpi::kStats>)
+  pick(gemm_row_tile<__VA_ARGS__, Epi::kPart>, gemm_row_tile<__VA_ARGS__, Epi::kSwiglu>,   \
+       gemm_row_tile<__VA_ARGS__, Epi::kStats>)
   if (p.cols == 256 && p.rows == 96)
     VIA_RT_PICK(6, 4, 1, 5, 6);
   else if (p.cols == 256)
@@ -1415,11 +1342,9 @@ int gate_up_blocks_per_group(int F) {
   return std::max(1, std::min(kWaves, (nblocks + 255) / 256));
 }
 
-int gemm_tiles(int N) { return (N + kTileN - 1) / kTileN; }
-
 GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K) {
-  if (!bf16) return GemmPath::kStaged;
-  if (M <= 32) return role == GemmRole::kHead ? GemmPath::kStaged : GemmPath::kStream;
+  if (!bf16) return GemmPath::kF32;
+  if (M <= 32) return role == GemmRole::kHead ? GemmPath::kHead : GemmPath::kStream;
   if (M <= 128 || role == GemmRole::kHead) return GemmPath::kRowTile;
   // 256 x 256 tiles take 178 us a round per 4096 of K, less than the two rounds
   // of row tiles they stand for, when there are enough of them
@@ -1431,8 +1356,8 @@ GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K) {
 int gemm_splits(GemmRole role, int M, int N, int K) { return row_tile_plan(role, M, N, K).ks; }
 
 int gemm_head_tiles(bool bf16, int M, int N, int K) {
-  if (gemm_path(bf16, GemmRole::kHead, M, N, K) != GemmPath::kRowTile) return gemm_tiles(N);
-  const int cols = row_tile_plan(GemmRole::kHead, M, N, K).cols;
+  if (gemm_path(bf16, GemmRole::kHead, M, N, K) == GemmPath::kHead) return gemm_tiles(N);
+  const int cols = bf16 ? row_tile_plan(GemmRole::kHead, M, N, K).cols : kF32HeadCols;
   return (N + cols - 1) / cols;
 }
 
@@ -1470,12 +1395,8 @@ void launch_gemm(bool bf16, GemmRole role, const GemmArgs& a, hipStream_t s, hip
       else
         launch_ki_part(a, s, e0, e1);
       break;
-    case GemmPath::kStaged:
-      if (bf16)
-        launch_gemm_head<uint16_t>(a, s, e0, e1);
-      else
-        launch_staged_f32(role, a, s, e0, e1);
-      break;
+    case GemmPath::kHead: launch_head(a, s, e0, e1); break;
+    case GemmPath::kF32: launch_f32(role, a, s, e0, e1); break;
   }
 }
 

@@ -51,8 +51,9 @@ void launch_gemm(bool bf16, GemmRole role, const GemmArgs& a, hipStream_t s, hip
 //   kRowTile  bf16, 33 rows and more (the head's only kernel there): LDS-fed
 //             tiles of 64 to 128 rows x 128 or 256 columns, gemm_splits K splits
 //   kPrefill  bf16, enough rows to fill the GPU with 256 x 256 tiles (one partial)
-//   kStaged   fp32 models, and the bf16 head of up to 32 rows
-enum class GemmPath { kStream, kRowTile, kPrefill, kStaged };
+//   kHead     the bf16 head of up to 32 rows
+//   kF32      every projection and size of fp32 models (one partial)
+enum class GemmPath { kStream, kRowTile, kPrefill, kHead, kF32 };
 GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K);
 // K splits (partial products) of the kRowTile kernel.
 int gemm_splits(GemmRole role, int M, int N, int K);
@@ -67,8 +68,6 @@ int gemm_head_tiles(bool bf16, int M, int N, int K);
 // Plain bf16 product a.part[M, N] = X[M, K] W[N, K]^T (one activation term)
 // on the prefill GEMM.
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
-// Column tiles (256 wide) of an N-column kStaged GEMM.
-int gemm_tiles(int N);
 // Blocks per work-group and K splits of the kStream kernels for an [N, K]
 // weight (about 256 work-groups).
 void gemm_ki_plan(int N, int K, int* nb, int* ksplit);

@@ -537,8 +537,8 @@ void launch_resid_add(bool bf16, float* X, const float* P, int ksplit, int M, in
     }
     return;
   }
-  if (!bf16) {
-    hipLaunchKernelGGL((resid_add_kernel<float, false, 1, 0>), grid, dim3(64), 0, s, X, P, ksplit, M, d,
+  if (!bf16) {  // one partial
+    hipLaunchKernelGGL((resid_add_kernel<float, false, 1, 1>), grid, dim3(64), 0, s, X, P, ksplit, M, d,
                        (const float*)g, Y, MBn, rows, ss, ss_stride, Xcopy, (const float*)E, erows);
     return;
   }
@@ -575,7 +575,7 @@ void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
       default: go(qkv_finish_kernel<uint16_t, 0>); break;
     }
   } else {
-    go(qkv_finish_kernel<float, 0>);
+    go(qkv_finish_kernel<float, 1>);
   }
 }
 

@@ -26,23 +26,14 @@ size_t al(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 int esize_of(const via_model_desc* d) { return d->dtype == VIA_DTYPE_BF16 ? 2 : 4; }
 
-// K splits of an fp32 model's GEMM: as many work-groups as fit the 256 compute
-// units in one round (a GEMM work-group occupies a whole CU, so a 257th would
-// run alone in a second round), with at least 8 steps of 32 per split.
-int choose_ksplit(int N, int K) {
-  const int tiles = gemm_tiles(N);
-  return std::max(1, std::min(256 / std::max(1, tiles), K / 256));
-}
-
 struct GemmShape {
-  int N, K, ks;
+  int N, K;
   GemmRole role;
   int nb_ki, ks_ki;  // the K-interleaved kernel's blocks per work-group and splits (forwards of <= 32 rows)
 
   // K splits of a forward of M rows
   int splits(bool bf16, int M) const {
     switch (gemm_path(bf16, role, M, N, K)) {
-      case GemmPath::kStaged: return ks;
       case GemmPath::kStream: return ks_ki;
       case GemmPath::kRowTile: return gemm_splits(role, M, N, K);
       default: return 1;
@@ -68,13 +59,13 @@ Dims dims_of(const via_model_desc* d) {
   r.G = r.H / std::max(1, r.KVH);
   const bool f32 = d->dtype != VIA_DTYPE_BF16;
   auto shape = [&](int N, int K, GemmRole role) {
-    GemmShape g{N, K, choose_ksplit(N, K), role, 1, 1};
+    GemmShape g{N, K, role, 1, 1};
     gemm_ki_plan(N, K, &g.nb_ki, &g.ks_ki);
     return g;
   };
   r.g_qkv = shape(r.qkv, r.d, GemmRole::kQkv);
   r.g_o = shape(r.d, r.H * r.hd, GemmRole::kO);
-  r.g_gu = GemmShape{2 * r.F, r.d, 1, GemmRole::kGateUp, 1, 1};  // full K per work-group (SwiGLU epilogue)
+  r.g_gu = GemmShape{2 * r.F, r.d, GemmRole::kGateUp, 1, 1};  // full K per work-group (SwiGLU epilogue)
   r.g_down = shape(r.d, r.F, GemmRole::kDown);
   return r;
 }
@@ -128,7 +119,7 @@ Layout layout_of(const via_model_desc* desc, int max_rows, int max_batch, int ma
   L.max_chunks = std::min(kAttnMaxSplits, ceil_div(max_blocks * kBlock, 32));
   L.att_o = take((size_t)L.max_chunks * R * D.H * D.hd * 4);
   L.att_ml = take((size_t)L.max_chunks * R * D.H * 2 * 4);
-  L.lm_part = take((size_t)ceil_div(D.V, 128) * R * 4 * 4);  // column tiles of 128 or 256
+  L.lm_part = take((size_t)ceil_div(D.V, 64) * R * 4 * 4);  // column tiles of 64, 128 or 256
   L.ss = take((size_t)ceil_div(D.d, kNormChunk) * R * 4);  // RMSNorm sums of squares [chunk][row]
   L.xstate = take((size_t)max_seqs * kStateRows * D.d * 4);
   L.max_items = ceil_div(max_rows * D.G, kAttnQueries) + max_batch;
