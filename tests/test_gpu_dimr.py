@@ -69,6 +69,25 @@ def test_dimr_cost_matches_fp64(rows, V, scale, T, alpha, beta, ld):
     assert (err <= tol).all(), (got, ref)
 
 
+@pytest.mark.parametrize("rows,V,ld", [
+    (2, 1, None), (2, 2047, None), (2, 2048, None), (2, 2051, 2052),   # no whole round of 2048 ids, one, one and an end
+    (2, 40961, 40964), (2, 57344, None), (2, 57345, 57347), (2, 65540, None),  # past the rounds kept in registers and LDS
+    (257, 2049, None), (257, 16390, 16392), (258, 24576, None), (257, 28673, 28675),  # the form of more than 256 rows
+])
+def test_dimr_cost_at_kept_round_edges(rows, V, ld):
+    """The sizes where the kernel keeps one more group of ids, re-reads the
+    rest, takes its many-row form, or (ld not a multiple of 4) reads unaligned
+    rows; bound as in test_dimr_cost_matches_fp64."""
+    print(f"[case] dimr_cost edges rows={rows} V={V} ld={ld}", flush=True)
+    g = torch.Generator().manual_seed(rows + V)
+    q = torch.randn(rows, V, generator=g) * 2.0
+    p = q + torch.randn(rows, V, generator=g)
+    got = gpu_cost(q, p, 0.8, 0.1, 1.1, ld)
+    ref = rkl_cost(q.double(), p.double(), 0.8, 0.1, 1.1)
+    lmax = (torch.cat([q, p]).abs().max().item() / 0.8 + math.log(V)) * 2
+    assert ((got - ref).abs() <= 1e-5 * ref.abs() + 8 * 2.0 ** -23 * lmax * 2 + 1e-6).all()
+
+
 def test_dimr_cost_rejects_bad_arguments():
     sp = C.c_void_p(0)
     buf = torch.zeros(64, dtype=torch.float32, device="cuda")
