@@ -731,51 +731,51 @@ void launch_ki_part(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t 
 }
 
 // ---------------------------------------------------------------- head stats
+// One work-group per head row; reductions by lane shuffles, then the four
+// waves in order.
 __global__ __launch_bounds__(256) void lm_finalize_kernel(const LmRow* lm, const float* part, int M, int ntiles,
                                                           float inv_T, int32_t* row_argmax, float* row_max,
                                                           float* row_sumexp, float* row_gap) {
-  __shared__ float s_mx[256], s_sc[256], s_se[256];
-  __shared__ int s_am[256];
-  const int m = blockIdx.x, t = threadIdx.x;
+  __shared__ float s_mx[4], s_sc[4], s_se[4];
+  __shared__ int s_am[4];
+  const int m = blockIdx.x, t = threadIdx.x, w = t >> 6;
+  const int out = lm[m].out;
   float mx = -INFINITY, sc = -INFINITY;
   int am = 0x7fffffff;
   for (int tl = t; tl < ntiles; tl += 256) {
-    const float* p = part + ((size_t)tl * M + m) * 4;
-    merge3(mx, am, sc, p[0], __float_as_int(p[3]), p[1]);
+    const float4 p = *(const float4*)(part + ((size_t)tl * M + m) * 4);
+    merge3(mx, am, sc, p.x, __float_as_int(p.w), p.y);
   }
-  s_mx[t] = mx;
-  s_sc[t] = sc;
-  s_am[t] = am;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float mx2 = __shfl_xor(mx, o, 64), sc2 = __shfl_xor(sc, o, 64);
+    const int am2 = __shfl_xor(am, o, 64);
+    merge3(mx, am, sc, mx2, am2, sc2);
+  }
+  if ((t & 63) == 0) {
+    s_mx[w] = mx;
+    s_sc[w] = sc;
+    s_am[w] = am;
+  }
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) {
-      float a_mx = s_mx[t], a_sc = s_sc[t];
-      int a_am = s_am[t];
-      merge3(a_mx, a_am, a_sc, s_mx[t + o], s_am[t + o], s_sc[t + o]);
-      s_mx[t] = a_mx;
-      s_sc[t] = a_sc;
-      s_am[t] = a_am;
-    }
-    __syncthreads();
-  }
-  const float gmx = s_mx[0];
+  mx = s_mx[0];
+  sc = s_sc[0];
+  am = s_am[0];
+#pragma unroll
+  for (int i = 1; i < 4; ++i) merge3(mx, am, sc, s_mx[i], s_am[i], s_sc[i]);
   float se = 0.f;
   for (int tl = t; tl < ntiles; tl += 256) {
     const float* p = part + ((size_t)tl * M + m) * 4;
-    se += p[2] * expf((p[0] - gmx) * inv_T);
+    se += p[2] * expf((p[0] - mx) * inv_T);
   }
-  s_se[t] = se;
+  se = wave_sum(se);
+  if ((t & 63) == 0) s_se[w] = se;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) s_se[t] += s_se[t + o];
-    __syncthreads();
-  }
   if (t == 0) {
-    const int out = lm[m].out;
-    row_max[out] = gmx;
-    row_argmax[out] = s_am[0];
-    row_sumexp[out] = s_se[0];
-    if (row_gap) row_gap[out] = gmx - s_sc[0];
+    row_max[out] = mx;
+    row_argmax[out] = am;
+    row_sumexp[out] = ((s_se[0] + s_se[1]) + s_se[2]) + s_se[3];
+    if (row_gap) row_gap[out] = mx - sc;
   }
 }
 

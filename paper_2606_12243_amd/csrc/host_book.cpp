@@ -526,7 +526,7 @@ int plan_attention(AttnItem* items, int n_items, int KVH, int max_splits, int ta
   // contexts with several query items per sequence) takes more work-groups
   if (span > kAttnPrefSpan * 3 / 2) span = kAttnPrefSpan;
   const int need = ((max_kv + 31) / 32 + max_splits - 1) / max_splits * 32;  // at most max_splits splits
-  span = std::max(span, need);
+  span = std::max({span, need, max_kv <= kAttnDirectKeys ? (max_kv + 31) / 32 * 32 : kAttnMinSpan});
   if (span > kAttnMaxSpan) return -1;
   // One round: when these spans leave more work-groups than the GPU has
   // compute units (ragged lengths round up to an extra split; a second

@@ -139,7 +139,11 @@ struct QkvArgs {
   const float* ss;     // RMSNorm sums of squares of the input rows (row_scale)
   int ss_stride, d;
   float eps;
+  double2* rope;       // [M][hd/2] rotations (cos, sin) of the rows' positions
+  int rope_own, rope_store;  // this launch computes them, and stores them for the later layers
 };
+// Forwards of up to this many rows compute the rotations in every layer.
+constexpr int kRopeOwnRows = 32;
 void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s);
 
 // Head statistics: combine the per-tile partials of every head row.

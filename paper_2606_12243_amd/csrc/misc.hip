@@ -264,7 +264,7 @@ __device__ __forceinline__ void qkv_store(const QkvArgs& a, const RowInfo& ri, i
   }
 }
 
-// The rotation angle of pair j at position pos, pos * theta^(-2j/hd), in fp64.
+// The rotation of pair j at position pos, pos * theta^(-2j/hd), in fp64.
 __device__ __forceinline__ void rope_angle(int pos, int j, const QkvArgs& a, double* sn, double* cs) {
   sincos((double)pos * pow((double)a.theta, -2.0 * (double)j / (double)a.hd), sn, cs);
 }
@@ -272,10 +272,12 @@ __device__ __forceinline__ void rope_angle(int pos, int j, const QkvArgs& a, dou
 // QKV partial sums -> RMSNorm scale of the input row -> rotate-half RoPE at
 // the row's position -> Q (bf16 hi/lo terms, or fp32) and paged K/V (model
 // dtype).  A work-group of 256 threads takes four (row, head of Q, K or V)
-// pairs, 64 threads each; thread j owns the rotation pair (j, j + hd/2) and
-// its angle pos * theta^(-2j/hd), computed in fp64 while the loads of the
-// pair's KS split partials (all in flight at once, summed in split order)
-// are outstanding.  KS = 0: the split count is taken from the arguments.
+// pairs, 64 threads each; thread j owns the rotation pair (j, j + hd/2), whose
+// rotation it computes (up to kRopeOwnRows rows, while the loads of the KS
+// split partials are outstanding; 8B, 32 rows: 5.2 us, reading it 5.4) or reads:
+// above, the forward's first layer leaves the rows' rotations in a table and the
+// others read it (256 rows: 12.6 -> 10.3 us).  KS = 0: the split count is taken
+// from the arguments.
 template <typename T, int KS>
 __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
   const int m = blockIdx.x, hh = blockIdx.y * 4 + (threadIdx.x >> 6), j = threadIdx.x & 63;
@@ -283,9 +285,19 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
   if (j >= half || hh >= a.H + 2 * a.KVH) return;
   const size_t N = (size_t)(a.H + 2 * a.KVH) * a.hd, stride = (size_t)a.M * N;
   const size_t c = (size_t)m * N + (size_t)hh * a.hd + j;
+  double2* rope = a.rope + (size_t)m * half + j;
   float x1 = 0.f, x2 = 0.f;
-  double cs = 1.0, sn = 0.0;
+  double2 cs_sn = make_double2(1.0, 0.0);
   const RowInfo ri = a.rows[m];
+  auto rotation = [&] {
+    if (hh >= a.H + a.KVH) return;  // V passes through
+    if (!a.rope_own) {
+      cs_sn = *rope;
+    } else {
+      rope_angle(ri.pos, j, a, &cs_sn.y, &cs_sn.x);
+      if (hh == 0 && a.rope_store) *rope = cs_sn;
+    }
+  };
   if constexpr (KS > 0) {
     float v1[KS], v2[KS];
 #pragma unroll
@@ -293,35 +305,43 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
       v1[q] = a.P[(size_t)q * stride + c];
       v2[q] = a.P[(size_t)q * stride + c + half];
     }
-    if (hh < a.H + a.KVH) rope_angle(ri.pos, j, a, &sn, &cs);
+    rotation();
 #pragma unroll
     for (int q = 0; q < KS; ++q) {
       x1 += v1[q];
       x2 += v2[q];
     }
   } else {
-    if (hh < a.H + a.KVH) rope_angle(ri.pos, j, a, &sn, &cs);
+    rotation();
     for (int q = 0; q < a.ksplit; ++q) {
       x1 += a.P[(size_t)q * stride + c];
       x2 += a.P[(size_t)q * stride + c + half];
     }
   }
   const float sc = row_scale(a.ss, a.ss_stride, m, a.d, a.eps);  // RMSNorm of the input row
-  qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, cs, sn);
+  qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, cs_sn.x, cs_sn.y);
 }
 
-// The same for many-row forwards (prefill): one work-group per row.  The
-// row's hd/2 angles are computed once and shared through LDS by all its Q and
-// K heads (the per-pair form recomputes each one H + KVH times, which makes
-// the fp64 transcendentals the cost at thousands of rows); consecutive
-// threads then take consecutive pairs of the row's heads.  Same arithmetic,
-// same results.
+// The same for many-row forwards (prefill): one work-group per row.  The row's
+// hd/2 rotations are computed (first layer) or read once and shared through
+// LDS by all its Q and K heads; consecutive threads then take consecutive pairs
+// of the row's heads.  Same arithmetic, same results.
 template <typename T>
 __global__ __launch_bounds__(256) void qkv_finish_rows_kernel(QkvArgs a) {
-  __shared__ double s_cs[64], s_sn[64];  // hd <= 128
+  __shared__ double2 rot[64];  // hd <= 128
   const int m = blockIdx.x, half = a.hd >> 1;
   const RowInfo ri = a.rows[m];
-  for (int j = threadIdx.x; j < half; j += 256) rope_angle(ri.pos, j, a, &s_sn[j], &s_cs[j]);
+  if (threadIdx.x < half) {
+    double2* rope = a.rope + (size_t)m * half + threadIdx.x;
+    double2 cs_sn;
+    if (a.rope_own) {
+      rope_angle(ri.pos, threadIdx.x, a, &cs_sn.y, &cs_sn.x);
+      if (a.rope_store) *rope = cs_sn;
+    } else {
+      cs_sn = *rope;
+    }
+    rot[threadIdx.x] = cs_sn;
+  }
   const float sc = row_scale(a.ss, a.ss_stride, m, a.d, a.eps);  // RMSNorm of the input row
   __syncthreads();
   const int nh = a.H + 2 * a.KVH;
@@ -334,35 +354,44 @@ __global__ __launch_bounds__(256) void qkv_finish_rows_kernel(QkvArgs a) {
       x1 += a.P[(size_t)q * stride + c];
       x2 += a.P[(size_t)q * stride + c + half];
     }
-    qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, s_cs[j], s_sn[j]);
+    qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, rot[j].x, rot[j].y);
   }
 }
 
-// Tier decision and gate walk for one sequence (App. B.1): every draft gets
-// its ratio confidence and tier; one lane then walks the draft chain/tree.
+// Tier decision and gate walk for one sequence (App. B.1), one wave: lane j
+// holds draft j (at most 64) with everything the walk may ask of it, loaded at
+// once; the walk itself is wave-uniform, on ballots over the lanes and single
+// lanes' values, so it waits for memory once and not at every node.
 __global__ __launch_bounds__(64) void decide_kernel(DecideArgs a) {
-  const int b = blockIdx.x;
+  const int b = blockIdx.x, lane = threadIdx.x;
   const StepSeq ss = a.seqs[b];
   const int D = a.max_drafts, B = a.batch;
   const int base = b * D;
   const bool have_full = a.f_row_max != nullptr && ss.full_ran;
-  for (int j = threadIdx.x; j < ss.n_drafts; j += 64) {
-    int out = b * a.max_rows + a.draft_row[base + j];
-    float c = expf((a.s_draft_logit[base + j] - a.s_row_max[out]) * a.inv_T);
-    int t;
+  const bool live = lane < ss.n_drafts;
+  int out = 0, parent = -2, tok = -1, s_arg = 0, f_arg = 0, tier = -1;
+  float conf = 0.f, f_max = 0.f;
+  if (live) {
+    out = b * a.max_rows + a.draft_row[base + lane];
+    parent = a.draft_parent[base + lane];
+    tok = a.draft_tok[base + lane];
+    s_arg = a.s_row_argmax[out];
+    if (have_full) {
+      f_max = a.f_row_max[out];
+      f_arg = a.f_row_argmax[out];
+    }
+    conf = expf((a.s_draft_logit[base + lane] - a.s_row_max[out]) * a.inv_T);
     if (a.forced >= 0)
-      t = a.forced;
-    else if (c >= a.tau_acc)
-      t = 0;
-    else if (c >= a.tau_full)
-      t = 1;
+      tier = a.forced;
+    else if (conf >= a.tau_acc)
+      tier = 0;
+    else if (conf >= a.tau_full)
+      tier = 1;
     else
-      t = 2;  // also a NaN confidence
-    a.conf[base + j] = c;
-    a.tier[base + j] = (int8_t)t;
+      tier = 2;  // also a NaN confidence
+    a.conf[base + lane] = conf;
+    a.tier[base + lane] = (int8_t)tier;
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
   int* status = a.packed;
   int* kappa = a.packed + B;
   int* emit = a.packed + 2 * B;
@@ -374,126 +403,92 @@ __global__ __launch_bounds__(64) void decide_kernel(DecideArgs a) {
     // kept with probability min(1, q(x) / ((1 - alpha) p(x))) (Eq. A.2),
     // accepted iff its uniform is below that, else it owes a sample of the
     // A.3 residual.  The owed sample is drawn by the sampling kernels.
-    int k = 0, st = 0;
-    SampleReq rq{0, 0, 0, 0.f};
-    for (int j = 0; j < ss.n_drafts; ++j) {
-      const int t = a.tier[base + j];
-      const int out = b * a.max_rows + a.draft_row[base + j];
-      if (t == 0) {
-        path[k++] = j;
-        continue;
+    bool keep = tier == 0, finite = true;
+    if (tier == 2 && have_full) {
+      finite = isfinite(f_max);
+      if (finite) {
+        const float qx = expf((a.f_draft_logit[base + lane] - f_max) * a.inv_T) / a.f_row_sumexp[out];
+        const float px = a.draft_probs[(size_t)(base + lane) * a.vocab + tok];
+        const float pk = px <= 0.f ? 1.f : fminf(1.f, qx / ((1.f - a.alpha) * px));
+        keep = a.u[(size_t)(base + lane) * 3] < pk;
       }
-      if (t == 1) {
-        rq = SampleReq{1, out, j, a.u[(size_t)(base + j) * 3 + 1]};
+    }
+    const unsigned long long stop = __ballot(live && !keep);
+    const int k = stop ? __ffsll((long long)stop) - 1 : ss.n_drafts;  // the first draft not kept
+    for (int q = lane; q < D; q += 64) path[q] = q < k ? q : -1;
+    if (lane != (stop ? k : 0)) return;
+    SampleReq rq{0, 0, 0, 0.f};
+    int st = 0;
+    if (stop) {
+      if (tier == 1)
+        rq = SampleReq{1, out, k, a.u[(size_t)(base + k) * 3 + 1]};
+      else if (!have_full)
+        st = 1;
+      else if (!finite)
+        st = 2;
+      else
+        rq = SampleReq{2, out, k, a.u[(size_t)(base + k) * 3 + 2]};
+    }
+    a.req[b] = rq;
+    status[b] = st;
+    kappa[b] = k;
+    emit[b] = -1;  // a sample owed is written by sample_pick_kernel
+    new_len[b] = st == 2 ? ss.n : ss.n + k + (rq.kind ? 1 : 0);
+    return;
+  }
+  // value v of draft j (wave-uniform)
+  auto of = [](int v, int j) { return __builtin_amdgcn_readlane(v, j); };
+  auto off = [](float v, int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j)); };
+  int u = -1, k = 0, em = -1, st = 0, step = -1;  // lane i keeps path entry i in `step`
+  for (;;) {
+    const unsigned long long kids = __ballot(live && parent == u);  // children of u, in draft order
+    if (!kids) break;                                               // leaf: whole path accepted, no emit
+    const int first = __ffsll((long long)kids) - 1;
+    int take = -1;
+    float best = 0.f;
+    for (unsigned long long acc = __ballot(live && parent == u && tier == 0); acc; acc &= acc - 1) {
+      const int j = __ffsll((long long)acc) - 1;
+      const float c = off(conf, j);
+      if (take < 0 || c > best) {
+        take = j;
+        best = c;
+      }
+    }
+    if (take < 0) {
+      if (__ballot(live && parent == u && tier == 1)) {
+        em = of(s_arg, first);
         break;
       }
       if (!have_full) {
         st = 1;
         break;
       }
-      const float fm = a.f_row_max[out];
-      if (!isfinite(fm)) {
+      if (!isfinite(off(f_max, first))) {  // non-finite logits of q
         st = 2;
         break;
       }
-      const float qx = expf((a.f_draft_logit[base + j] - fm) * a.inv_T) / a.f_row_sumexp[out];
-      const float px = a.draft_probs[(size_t)(base + j) * a.vocab + a.draft_tok[base + j]];
-      const float keep = px <= 0.f ? 1.f : fminf(1.f, qx / ((1.f - a.alpha) * px));
-      if (a.u[(size_t)(base + j) * 3] < keep) {
-        path[k++] = j;
-        continue;
-      }
-      rq = SampleReq{2, out, j, a.u[(size_t)(base + j) * 3 + 2]};
-      break;
-    }
-    if (st != 0) rq.kind = 0;
-    a.req[b] = rq;
-    status[b] = st;
-    kappa[b] = k;
-    emit[b] = -1;  // a sample owed is written by sample_pick_kernel
-    new_len[b] = st == 2 ? ss.n : ss.n + k + (rq.kind ? 1 : 0);
-    for (int q = k; q < D; ++q) path[q] = -1;
-    return;
-  }
-  int u = -1, k = 0, em = -1, st = 0;
-  for (;;) {
-    // children of u, in draft order
-    int best_acc = -1, any_slim = 0, first_kid = -1, nk = 0;
-    float best_c = 0.f;
-    int kids[kMaxChildren * 8];
-    for (int j = 0; j < ss.n_drafts; ++j) {
-      if (a.draft_parent[base + j] != u) continue;
-      if (first_kid < 0) first_kid = j;
-      if (nk < kMaxChildren * 8) kids[nk++] = j;
-      int t = a.tier[base + j];
-      float c = a.conf[base + j];
-      if (t == 0 && (best_acc < 0 || c > best_c)) {
-        best_acc = j;
-        best_c = c;
-      }
-      if (t == 1) any_slim = 1;
-    }
-    if (first_kid < 0) break;  // leaf: whole path accepted, no emit
-    const int out = b * a.max_rows + a.draft_row[base + first_kid];
-    if (best_acc >= 0) {
-      path[k++] = best_acc;
-      u = best_acc;
-      continue;
-    }
-    if (any_slim) {
-      em = a.s_row_argmax[out];
-      break;
-    }
-    if (!have_full) {
-      st = 1;
-      break;
-    }
-    float fm = a.f_row_max[out];
-    if (!isfinite(fm)) {  // non-finite logits of q
-      st = 2;
-      break;
-    }
-    int gtok = a.f_row_argmax[out], take = -1;
-    for (int q = 0; q < nk; ++q)
-      if (a.draft_tok[base + kids[q]] == gtok) {
-        take = kids[q];
+      const int gtok = of(f_arg, first);
+      const unsigned long long hit = __ballot(live && parent == u && tok == gtok);
+      if (!hit) {
+        em = gtok;
         break;
       }
-    if (take >= 0) {
-      path[k++] = take;
-      u = take;
-      continue;
+      take = __ffsll((long long)hit) - 1;
     }
-    em = gtok;
-    break;
+    if (lane == k) step = take;
+    ++k;
+    u = take;
   }
   const int ev = st == 0 ? em : -1;
   const int nv = st == 2 ? ss.n : ss.n + k + (st == 0 && em >= 0 ? 1 : 0);
-  status[b] = st;
-  kappa[b] = k;
-  emit[b] = ev;
-  new_len[b] = nv;
-  for (int q = k; q < D; ++q) path[q] = -1;
-  if (a.h_packed) {
-    // the host mirror, written past the caches so that it is in host memory
-    // once the stream has been synchronised.  Values come from registers
-    // (the path in rounds of 8 loads, then 8 stores): a value re-read from
-    // device memory after each store would make every system-scope store
-    // wait for a load, one host round trip per value.
-    auto put = [&](int i, int v) { __hip_atomic_store(a.h_packed + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
-    put(b, st);
-    put(B + b, k);
-    put(2 * B + b, ev);
-    put(3 * B + b, nv);
-    for (int q0 = 0; q0 < D; q0 += 8) {
-      int pv[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pv[j] = q0 + j < D ? path[q0 + j] : 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (q0 + j < D) put(4 * B + base + q0 + j, pv[j]);
-    }
-  }
+  // the host mirror is written past the caches, so that it is in host memory
+  // once the stream has been synchronised
+  auto put = [&](int i, int v) {
+    a.packed[i] = v;
+    if (a.h_packed) __hip_atomic_store(a.h_packed + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  if (lane < 4) put(lane * B + b, lane == 0 ? st : lane == 1 ? k : lane == 2 ? ev : nv);
+  for (int q = lane; q < D; q += 64) put(4 * B + base + q, q < k ? step : -1);
 }
 
 // Tree compaction: copy the K/V of slot src to slot dst in every layer slot.
@@ -516,14 +511,11 @@ __global__ __launch_bounds__(128) void kv_move_kernel(T* pool, int nblk, int KVH
 
 }  // namespace
 
-// Rows from which the residual update takes its many-row form.
-constexpr int kResidRowsMin = 128;
-
 void launch_resid_add(bool bf16, float* X, const float* P, int ksplit, int M, int d, const void* g, void* Y, int MBn,
                       const RowInfo* rows, float* ss, int ss_stride, hipStream_t s, float* Xcopy, const void* E,
                       const RowInfo* erows) {
   const dim3 grid((d + kNormChunk - 1) / kNormChunk, M);
-  if (bf16 && P && !rows && !E && M >= kResidRowsMin && (ksplit == 1 || ksplit == 2 || ksplit == 4 || ksplit == 8)) {
+  if (bf16 && P && !rows && !E && M > kManyRows && (ksplit == 1 || ksplit == 2 || ksplit == 4 || ksplit == 8)) {
     const dim3 rgrid((d + kNormChunk - 1) / kNormChunk, (M + 15) / 16);
     auto go = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, rgrid, dim3(256), 0, s, X, P, M, d, (const uint16_t*)g, Y, MBn, ss, ss_stride, Xcopy,

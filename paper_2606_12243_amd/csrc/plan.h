@@ -11,6 +11,12 @@ constexpr int kMaxChildren = 8;   // drafts verified by one row
 constexpr int kAttnMaxSplits = 32;  // key splits per sequence (partials one query's combine merges)
 constexpr int kAttnMaxSpan = 8192;  // keys of one split (pages of a split's work-group, x16)
 constexpr int kAttnPrefSpan = 4096;  // keys per work-group beyond which a forward takes more work-groups than the target
+// Keys of a split at least: one 32-key block for each of the four waves (1B shape,
+// 1032 keys: 64-key splits 8.6 + 4.8 us with their combine, 128 8.7 + 4.1, 160 10.2 + 4.0).
+constexpr int kAttnMinSpan = 128;
+// Up to here one split per item, written directly: a wave's two further blocks
+// take 1.6 us each, the combine and its launch 5.
+constexpr int kAttnDirectKeys = 384;
 constexpr int kAttnTargetGroups = 192;  // attention work-groups a forward aims for (fewer, longer spans than one per compute unit: measured best at the 8B shapes)
 constexpr int kAttnQueries = 32;  // (row, head-in-group) queries per attention work-group
 constexpr int kNormChunk = 512;   // columns per partial sum of squares (RMSNorm)

@@ -71,7 +71,7 @@ Dims dims_of(const via_model_desc* d) {
 }
 
 struct Layout {
-  size_t X, Yf, Q, Af, Hf, Ylf, part, att_o, att_ml, lm_part, ss;
+  size_t X, Yf, Q, Af, Hf, Ylf, part, att_o, att_ml, lm_part, ss, rope;
   size_t xstate;                       // state ring: [max_seqs][kStateRows][d] residual stream after the shared layers
   size_t rows, seqs, btab, items, lm, xfer;  // plan region
   size_t step_seqs, dtok, drow, dpar, du;  // step region
@@ -121,6 +121,7 @@ Layout layout_of(const via_model_desc* desc, int max_rows, int max_batch, int ma
   L.att_ml = take((size_t)L.max_chunks * R * D.H * 2 * 4);
   L.lm_part = take((size_t)ceil_div(D.V, 64) * R * 4 * 4);  // column tiles of 64, 128 or 256
   L.ss = take((size_t)ceil_div(D.d, kNormChunk) * R * 4);  // RMSNorm sums of squares [chunk][row]
+  L.rope = take(R * (D.hd / 2) * sizeof(double2));  // rotations of the rows' positions
   L.xstate = take((size_t)max_seqs * kStateRows * D.d * 4);
   L.max_items = ceil_div(max_rows * D.G, kAttnQueries) + max_batch;
   // plan region (one upload per forward)
@@ -428,10 +429,13 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
   qa.ss_stride = ss_stride;
   qa.d = D.d;
   qa.eps = eps;
+  qa.rope = (double2*)(ws + L.rope);
   for (size_t si = start_si; si < route.size(); ++si) {
     const int l = route[si];
     gemm(Yf, m->w_qkv[l], D.g_qkv, GemmRole::kQkv, VIA_KERNEL_QKV);
     qa.layer_slot = (int)si;
+    qa.rope_own = M <= kRopeOwnRows || (int)si == start_si;
+    qa.rope_store = M > kRopeOwnRows && (int)si == start_si;
     launch_qkv_finish(bf, qa, s);
     at.layer_slot = (int)si;
     timed_launch(kv, VIA_KERNEL_ATTN, s, [&] { launch_attention(bf, at, s); });
