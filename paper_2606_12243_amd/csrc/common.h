@@ -108,11 +108,19 @@ __device__ __forceinline__ void put_afrag(void* base, int m, int k0, const float
 
 // RMSNorm scale of row m, 1/sqrt(mean(x^2) + eps), from the per-chunk sums
 // of squares ss[c * stride + m], c < ceil(d / kNormChunk), added in chunk
-// order.
+// order.  Eight chunks are loaded at a time (past the last: again, dropped by
+// the select): as a loop over the chunks the loads ran one after another, 4 us
+// at d = 4096 in every kernel that calls this.
 __device__ __forceinline__ float row_scale(const float* ss, int stride, int m, int d, float eps) {
   float t = 0.f;
   const int nch = (d + kNormChunk - 1) / kNormChunk;
-  for (int c = 0; c < nch; ++c) t += ss[(size_t)c * stride + m];
+  for (int c0 = 0; c0 < nch; c0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = ss[(size_t)min(c0 + i, nch - 1) * stride + m];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t += c0 + i < nch ? v[i] : 0.f;
+  }
   return 1.0f / sqrtf(t / (float)d + eps);
 }
 

@@ -51,6 +51,26 @@ __device__ __forceinline__ void split_sum2(const float* P, size_t stride, int ks
   }
 }
 
+// Eight consecutive norm gains (the caller's pointer may have any alignment).
+__device__ __forceinline__ void load_gain8(const uint16_t* g, float (&v)[8]) {
+  if (((uintptr_t)g & 15) == 0) {  // uniform: k0 is a multiple of 8
+    const uint4 w = *(const uint4*)g;
+    const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[2 * e] = __uint_as_float(u[e] << 16);
+      v[2 * e + 1] = __uint_as_float(u[e] & 0xFFFF0000u);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = bf2f(g[e]);
+  }
+}
+__device__ __forceinline__ void load_gain8(const float* g, float (&v)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = g[e];
+}
+
 // Residual update and RMSNorm gain, elementwise: x = X[m] + sum_s P[s][m]
 // (split order; P may be null), X[m] = x, and x * g is written as
 // activation fragments (to fragment row rows[m].lm when `rows` is given;
@@ -58,7 +78,8 @@ __device__ __forceinline__ void split_sum2(const float* P, size_t stride, int ks
 // is a per-row factor that commutes with the next projection, so its
 // consumer applies it (row_scale) after the GEMM; here each work-group adds
 // the sum of x^2 over its kNormChunk columns to ss[chunk][out].
-// Grid (ceil(d / kNormChunk), M), 64 threads of 8 columns each.
+// Grid (ceil(d / kNormChunk), M), 64 threads of 8 columns each.  The partials,
+// the row and the gains are loaded together: one wait for memory, not one each.
 template <typename G, bool BF16, int NT, int KS>
 __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P, int ksplit, int M, int d,
                                                        const G* g, void* Y, int MBn, const RowInfo* rows,
@@ -74,12 +95,11 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
   }
   const size_t stride = (size_t)M * d;
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float sq = 0.f;
+  float sq = 0.f, gain[8];
   if (k0 < d && E) {
     // embedding rows: X[m] = E[tok]
-    const G* e = E + (size_t)erows[m].tok * d + k0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = to_f<G>(e[i]);
+    load_gain8(g + k0, gain);
+    load_gain8(E + (size_t)erows[m].tok * d + k0, v);
     *(float4*)(x + k0) = make_float4(v[0], v[1], v[2], v[3]);
     *(float4*)(x + k0 + 4) = make_float4(v[4], v[5], v[6], v[7]);
     if (Xcopy) {
@@ -89,16 +109,21 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
 #pragma unroll
     for (int i = 0; i < 8; ++i) sq += v[i] * v[i];
   } else if (k0 < d) {
-    float4 acc[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+    float4 acc[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)}, u[2];
     if constexpr (KS > 0) {
       // exactly KS splits: all loads in flight, then summed in split order
+      float4 v0[KS], v1[KS];
       if (P) {
-        float4 v0[KS], v1[KS];
 #pragma unroll
         for (int q = 0; q < KS; ++q) {
           v0[q] = *(const float4*)(P + (size_t)q * stride + (size_t)m * d + k0);
           v1[q] = *(const float4*)(P + (size_t)q * stride + (size_t)m * d + k0 + 4);
         }
+      }
+      u[0] = *(float4*)(x + k0);
+      u[1] = *(float4*)(x + k0 + 4);
+      load_gain8(g + k0, gain);
+      if (P) {
 #pragma unroll
         for (int q = 0; q < KS; ++q) {
           acc[0].x += v0[q].x;
@@ -113,22 +138,24 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
       }
     } else {
       if (P) split_sum2(P, stride, ksplit, 0, (size_t)m * d + k0, (size_t)m * d + k0 + 4, acc[0], acc[1]);
+      u[0] = *(float4*)(x + k0);
+      u[1] = *(float4*)(x + k0 + 4);
+      load_gain8(g + k0, gain);
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      float4 u = *(float4*)(x + k0 + 4 * h);
       if (P) {
-        u.x = u.x + acc[h].x;
-        u.y = u.y + acc[h].y;
-        u.z = u.z + acc[h].z;
-        u.w = u.w + acc[h].w;
-        *(float4*)(x + k0 + 4 * h) = u;
+        u[h].x = u[h].x + acc[h].x;
+        u[h].y = u[h].y + acc[h].y;
+        u[h].z = u[h].z + acc[h].z;
+        u[h].w = u[h].w + acc[h].w;
+        *(float4*)(x + k0 + 4 * h) = u[h];
       }
-      if (Xcopy) *(float4*)(Xcopy + k0 + 4 * h) = u;
-      v[4 * h + 0] = u.x;
-      v[4 * h + 1] = u.y;
-      v[4 * h + 2] = u.z;
-      v[4 * h + 3] = u.w;
+      if (Xcopy) *(float4*)(Xcopy + k0 + 4 * h) = u[h];
+      v[4 * h + 0] = u[h].x;
+      v[4 * h + 1] = u[h].y;
+      v[4 * h + 2] = u[h].z;
+      v[4 * h + 3] = u[h].w;
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) sq += v[e] * v[e];
@@ -138,7 +165,7 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
   if (threadIdx.x == 0) ss[(size_t)chunk * ss_stride + out] = sq;
   if (k0 >= d) return;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = v[e] * to_f<G>(g[k0 + e]);
+  for (int e = 0; e < 8; ++e) v[e] = v[e] * gain[e];
   put_afrag<BF16, NT>(Y, out, k0, v, d >> 5, MBn);
 }
 
@@ -180,10 +207,12 @@ __global__ __launch_bounds__(256) void resid_add_rows_kernel(float* X, const flo
       b[q][0] = *(const float4*)(a + q * stride);
       b[q][1] = *(const float4*)(a + q * stride + 4);
     }
-    float v[8];
+    float v[8], gain[8];
+    float4 xv[2] = {*(float4*)x, *(float4*)(x + 4)};
+    load_gain8(g + k0, gain);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      float4 u = *(float4*)(x + 4 * h), s = make_float4(0.f, 0.f, 0.f, 0.f);
+      float4 u = xv[h], s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int q = 0; q < KS; ++q) {
         s.x += b[q][h].x;
@@ -207,7 +236,7 @@ __global__ __launch_bounds__(256) void resid_add_rows_kernel(float* X, const flo
     for (int e = 0; e < 8; ++e) sq += v[e] * v[e];
     p[i] = sq;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = v[e] * to_f<uint16_t>(g[k0 + e]);
+    for (int e = 0; e < 8; ++e) v[e] = v[e] * gain[e];
     put_afrag<true, NT>(Y, m, k0, v, d >> 5, MBn);
   }
   // wave_sum over the one-row form's threads T = 4 s + j: lane xor 32 and 16
