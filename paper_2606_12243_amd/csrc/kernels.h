@@ -140,10 +140,12 @@ struct QkvArgs {
   int ss_stride, d;
   float eps;
   double2* rope;       // [M][hd/2] rotations (cos, sin) of the rows' positions
-  int rope_own, rope_store;  // this launch computes them, and stores them for the later layers
+                       // (forwards of more than kRopeOwnRows rows)
 };
-// Forwards of up to this many rows compute the rotations in every layer.
+// Forwards of up to this many rows compute the rotations in every layer, others
+// once, into a.rope.
 constexpr int kRopeOwnRows = 32;
+void launch_rope_table(const QkvArgs& a, hipStream_t s);
 void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s);
 
 // Head statistics: combine the per-tile partials of every head row.

@@ -2,6 +2,7 @@
 // of the split-K GEMM partials (residual + RMSNorm, SwiGLU, QKV RoPE + paged
 // K/V write), the tier decision with its gate walk, and tree-path K/V
 // compaction.
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -302,11 +303,9 @@ __device__ __forceinline__ void rope_angle(int pos, int j, const QkvArgs& a, dou
 // the row's position -> Q (bf16 hi/lo terms, or fp32) and paged K/V (model
 // dtype).  A work-group of 256 threads takes four (row, head of Q, K or V)
 // pairs, 64 threads each; thread j owns the rotation pair (j, j + hd/2), whose
-// rotation it computes (up to kRopeOwnRows rows, while the loads of the KS
-// split partials are outstanding; 8B, 32 rows: 5.2 us, reading it 5.4) or reads:
-// above, the forward's first layer leaves the rows' rotations in a table and the
-// others read it (256 rows: 12.6 -> 10.3 us).  KS = 0: the split count is taken
-// from the arguments.
+// rotation it computes while the loads of the KS split partials are outstanding
+// (8B, 32 rows: 5.2 us; reading it from a table 5.4).  KS = 0: the split count is
+// taken from the arguments.
 template <typename T, int KS>
 __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
   const int m = blockIdx.x, hh = blockIdx.y * 4 + (threadIdx.x >> 6), j = threadIdx.x & 63;
@@ -314,18 +313,11 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
   if (j >= half || hh >= a.H + 2 * a.KVH) return;
   const size_t N = (size_t)(a.H + 2 * a.KVH) * a.hd, stride = (size_t)a.M * N;
   const size_t c = (size_t)m * N + (size_t)hh * a.hd + j;
-  double2* rope = a.rope + (size_t)m * half + j;
   float x1 = 0.f, x2 = 0.f;
   double2 cs_sn = make_double2(1.0, 0.0);
   const RowInfo ri = a.rows[m];
   auto rotation = [&] {
-    if (hh >= a.H + a.KVH) return;  // V passes through
-    if (!a.rope_own) {
-      cs_sn = *rope;
-    } else {
-      rope_angle(ri.pos, j, a, &cs_sn.y, &cs_sn.x);
-      if (hh == 0 && a.rope_store) *rope = cs_sn;
-    }
+    if (hh < a.H + a.KVH) rope_angle(ri.pos, j, a, &cs_sn.y, &cs_sn.x);  // V passes through
   };
   if constexpr (KS > 0) {
     float v1[KS], v2[KS];
@@ -351,39 +343,120 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
   qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, cs_sn.x, cs_sn.y);
 }
 
-// The same for many-row forwards (prefill): one work-group per row.  The row's
-// hd/2 rotations are computed (first layer) or read once and shared through
-// LDS by all its Q and K heads; consecutive threads then take consecutive pairs
-// of the row's heads.  Same arithmetic, same results.
-template <typename T>
-__global__ __launch_bounds__(256) void qkv_finish_rows_kernel(QkvArgs a) {
-  __shared__ double2 rot[64];  // hd <= 128
-  const int m = blockIdx.x, half = a.hd >> 1;
-  const RowInfo ri = a.rows[m];
-  if (threadIdx.x < half) {
-    double2* rope = a.rope + (size_t)m * half + threadIdx.x;
-    double2 cs_sn;
-    if (a.rope_own) {
-      rope_angle(ri.pos, threadIdx.x, a, &cs_sn.y, &cs_sn.x);
-      if (a.rope_store) *rope = cs_sn;
-    } else {
-      cs_sn = *rope;
+// Rotations of the rows of a forward of more than kRopeOwnRows rows, computed
+// once for all its layers: grid (M), one thread per pair.
+__global__ __launch_bounds__(64) void rope_table_kernel(QkvArgs a) {
+  const int m = blockIdx.x, j = threadIdx.x, half = a.hd >> 1;
+  if (j >= half) return;
+  double2 cs_sn;
+  rope_angle(a.rows[m].pos, j, a, &cs_sn.y, &cs_sn.x);
+  a.rope[(size_t)m * half + j] = cs_sn;
+}
+
+// The QKV finish of such forwards.  A work-group takes 16 consecutive rows and
+// one KV head's share of them, its G query heads, its K head and its V head (or,
+// where that leaves compute units idle, some of them).  Thread t holds row t / 16
+// and the 8 dims from (t % 16) * 8 (hd 64: two heads' worth at a time), so the
+// partials are read 32 bytes a thread, a pass ahead of their use; the
+// rotations, the same for every head, stay in registers, and the rotation's
+// other half comes from the lane hd / 16 away; Q terms and K go out 16 bytes a
+// thread.  V, transposed in its pages, goes through LDS: 16 lanes then write 16
+// tokens of one dim next to each other, where a row per work-group left every V
+// page's 32-byte pieces to 16 work-groups on 8 XCDs (8B, 8188 rows: 134 us).
+template <typename T, int HD, int KS>
+__global__ __launch_bounds__(256) void qkv_finish_tile_kernel(QkvArgs a) {
+  constexpr int TPH = HD / 8, HPP = 16 / TPH;  // threads of a row per head; heads per pass
+  const int r = threadIdx.x >> 4, l = threadIdx.x & 15, sub = l / TPH, d0 = (l % TPH) * 8, half = HD / 2;
+  const int m = blockIdx.x * 16 + r, g = blockIdx.y, G = a.H / a.KVH;
+  const bool live = m < a.M;
+  const int mm = live ? m : a.M - 1;  // rows past the end repeat the last one and store nothing
+  const size_t N = (size_t)(a.H + 2 * a.KVH) * HD, stride = (size_t)a.M * N;
+  __shared__ float vt[HD][17];
+  // heads of this work-group: 0 .. G - 1 its queries, G the K head, G + 1 the V head
+  auto head = [&](int h) { return h < G ? g * G + h : h == G ? a.H + g : a.H + a.KVH + g; };
+  float4 v[KS][2];
+  auto load = [&](int h0) {
+    const float* p = a.P + (size_t)mm * N + (size_t)head(min(h0 + sub, G + 1)) * HD + d0;
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      v[q][0] = *(const float4*)(p + q * stride);
+      v[q][1] = *(const float4*)(p + q * stride + 4);
     }
-    rot[threadIdx.x] = cs_sn;
-  }
-  const float sc = row_scale(a.ss, a.ss_stride, m, a.d, a.eps);  // RMSNorm of the input row
-  __syncthreads();
-  const int nh = a.H + 2 * a.KVH;
-  const size_t N = (size_t)nh * a.hd, stride = (size_t)a.M * N;
-  for (int e = threadIdx.x; e < nh * half; e += 256) {
-    const int hh = e / half, j = e - hh * half;
-    const size_t c = (size_t)m * N + (size_t)hh * a.hd + j;
-    float x1 = 0.f, x2 = 0.f;
-    for (int q = 0; q < a.ksplit; ++q) {
-      x1 += a.P[(size_t)q * stride + c];
-      x2 += a.P[(size_t)q * stride + c + half];
+  };
+  load(blockIdx.z * HPP);
+  double2 rot[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) rot[e] = a.rope[(size_t)mm * half + d0 % half + e];
+  const RowInfo ri = a.rows[mm];
+  const int blk = ri.blk, t = ri.slot % kBlock;
+  const float sc = row_scale(a.ss, a.ss_stride, mm, a.d, a.eps);  // RMSNorm of the input row
+  const bool first = d0 < half;
+  for (int h0 = blockIdx.z * HPP; h0 < G + 2; h0 += gridDim.z * HPP) {
+    const int h = h0 + sub, hh = head(min(h, G + 1));
+    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      x[0] += v[q][0].x;
+      x[1] += v[q][0].y;
+      x[2] += v[q][0].z;
+      x[3] += v[q][0].w;
+      x[4] += v[q][1].x;
+      x[5] += v[q][1].y;
+      x[6] += v[q][1].z;
+      x[7] += v[q][1].w;
     }
-    qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, rot[j].x, rot[j].y);
+    if (h0 + (int)gridDim.z * HPP < G + 2) load(h0 + gridDim.z * HPP);
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      x[e] *= sc;
+      const float o = __shfl_xor(x[e], TPH / 2, 64);  // the pair's other half
+      const double x1 = first ? x[e] : o, x2 = first ? o : x[e];
+      const float ro = first ? (float)(x1 * rot[e].x - x2 * rot[e].y) : (float)(x2 * rot[e].x + x1 * rot[e].y);
+      y[e] = h <= G ? ro : x[e];  // V passes through
+    }
+    if (live && h < G) {
+      const size_t o = ((size_t)m * a.H + hh) * HD + d0;
+      if constexpr (sizeof(T) == 2) {
+        // bf16 hi (truncated) + lo (rounded) terms for the attention MFMAs
+        uint32_t hw[4], lw[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t u0 = __float_as_uint(y[2 * e]) >> 16, u1 = __float_as_uint(y[2 * e + 1]) >> 16;
+          hw[e] = pack_bf16x2(u0, u1);
+          lw[e] = pack_bf16x2(f2bf(y[2 * e] - __uint_as_float(u0 << 16)), f2bf(y[2 * e + 1] - __uint_as_float(u1 << 16)));
+        }
+        *(uint4*)(a.q_hi + o) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+        *(uint4*)(a.q_lo + o) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+      } else {
+        float* q = (float*)a.q_hi + o;
+        *(float4*)q = make_float4(y[0], y[1], y[2], y[3]);
+        *(float4*)(q + 4) = make_float4(y[4], y[5], y[6], y[7]);
+      }
+    } else if (live && h == G) {
+      T* kp = (T*)a.pool + k_off(a.layer_slot, blk, a.pool_blocks, a.KVH, HD, g, t, d0);
+      if constexpr (sizeof(T) == 2) {
+        *(uint4*)kp = make_uint4(pack_bf16x2(f2bf(y[0]), f2bf(y[1])), pack_bf16x2(f2bf(y[2]), f2bf(y[3])),
+                                 pack_bf16x2(f2bf(y[4]), f2bf(y[5])), pack_bf16x2(f2bf(y[6]), f2bf(y[7])));
+      } else {
+        *(float4*)kp = make_float4(y[0], y[1], y[2], y[3]);
+        *(float4*)(kp + 4) = make_float4(y[4], y[5], y[6], y[7]);
+      }
+    }
+    if (h0 <= G + 1 && G + 1 < h0 + HPP) {  // uniform: this pass holds the V head
+      if (h == G + 1) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vt[d0 + e][r] = y[e];
+      }
+      __syncthreads();
+      // lane -> token threadIdx.x % 16, dims threadIdx.x / 16, + 16, ...
+      const int vr = threadIdx.x & 15, vm = blockIdx.x * 16 + vr;
+      if (vm < a.M) {
+        const RowInfo vi = a.rows[vm];
+        T* vp = (T*)a.pool + v_off(a.layer_slot, vi.blk, a.pool_blocks, a.KVH, HD, g, vi.slot % kBlock, 0);
+        for (int d = threadIdx.x >> 4; d < HD; d += 16) vp[(size_t)d * kBlock] = from_f<T>(vt[d][vr]);
+      }
+    }
   }
 }
 
@@ -577,12 +650,26 @@ void launch_resid_add(bool bf16, float* X, const float* P, int ksplit, int M, in
   }
 }
 
+void launch_rope_table(const QkvArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(rope_table_kernel, dim3(a.M), dim3(64), 0, s, a);
+}
+
 void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
-  if (a.M > kManyRows && a.hd <= 128) {  // many rows: angles shared per row
-    if (bf16)
-      hipLaunchKernelGGL(qkv_finish_rows_kernel<uint16_t>, dim3(a.M), dim3(256), 0, s, a);
+  if (a.M > kRopeOwnRows && (a.ksplit == 1 || a.ksplit == 2 || a.ksplit == 4 || a.ksplit == 8)) {
+    const int tiles = (a.M + 15) / 16, heads = a.H / a.KVH + 2, passes = a.hd == 128 ? heads : (heads + 1) / 2;
+    const dim3 grid(tiles, a.KVH, std::min(passes, (256 + tiles * a.KVH - 1) / (tiles * a.KVH)));
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
+    auto by_size = [&](auto k128, auto k64) { a.hd == 128 ? go(k128) : go(k64); };
+    if (!bf16)  // one partial
+      by_size(qkv_finish_tile_kernel<float, 128, 1>, qkv_finish_tile_kernel<float, 64, 1>);
+    else if (a.ksplit == 1)
+      by_size(qkv_finish_tile_kernel<uint16_t, 128, 1>, qkv_finish_tile_kernel<uint16_t, 64, 1>);
+    else if (a.ksplit == 2)
+      by_size(qkv_finish_tile_kernel<uint16_t, 128, 2>, qkv_finish_tile_kernel<uint16_t, 64, 2>);
+    else if (a.ksplit == 4)
+      by_size(qkv_finish_tile_kernel<uint16_t, 128, 4>, qkv_finish_tile_kernel<uint16_t, 64, 4>);
     else
-      hipLaunchKernelGGL(qkv_finish_rows_kernel<float>, dim3(a.M), dim3(256), 0, s, a);
+      by_size(qkv_finish_tile_kernel<uint16_t, 128, 8>, qkv_finish_tile_kernel<uint16_t, 64, 8>);
     return;
   }
   const dim3 grid(a.M, (a.H + 2 * a.KVH + 3) / 4);
@@ -592,7 +679,6 @@ void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
       case 1: go(qkv_finish_kernel<uint16_t, 1>); break;
       case 2: go(qkv_finish_kernel<uint16_t, 2>); break;
       case 4: go(qkv_finish_kernel<uint16_t, 4>); break;
-      case 8: go(qkv_finish_kernel<uint16_t, 8>); break;
       default: go(qkv_finish_kernel<uint16_t, 0>); break;
     }
   } else {

@@ -430,12 +430,11 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
   qa.d = D.d;
   qa.eps = eps;
   qa.rope = (double2*)(ws + L.rope);
+  if (M > kRopeOwnRows) launch_rope_table(qa, s);
   for (size_t si = start_si; si < route.size(); ++si) {
     const int l = route[si];
     gemm(Yf, m->w_qkv[l], D.g_qkv, GemmRole::kQkv, VIA_KERNEL_QKV);
     qa.layer_slot = (int)si;
-    qa.rope_own = M <= kRopeOwnRows || (int)si == start_si;
-    qa.rope_store = M > kRopeOwnRows && (int)si == start_si;
     launch_qkv_finish(bf, qa, s);
     at.layer_slot = (int)si;
     timed_launch(kv, VIA_KERNEL_ATTN, s, [&] { launch_attention(bf, at, s); });
