@@ -409,8 +409,8 @@ via_status via_sample_rows(via_kv *kv, const via_verify_out *out, int32_t out_ro
 /* via_sample_rows for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same draws and probabilities, without a KV handle.  The requests go to
- * the device as kernel arguments and the kernels' scratch (request array and
- * per-slice sums, 66560 bytes) is a static device array of the library, which
+ * the device as kernel arguments and the kernels' scratch (per-slice sums,
+ * 65536 bytes) is a static device array of the library, which
  * each GPU it runs on holds until the process ends; the call allocates and
  * frees nothing.  Every call on a GPU reuses that GPU's scratch and leaves its
  * contents behind: calls that overlap on one GPU (two streams, two threads)

@@ -731,10 +731,6 @@ __device__ inline SampleRow sample_row(const DecideArgs& a, const SampleReq& r, 
   w.inv_beta = 1.f / a.beta;
   return w;
 }
-// q-weight of id v (kind 1: unnormalised q', kind 2: q)
-__device__ inline float q_weight(const SampleRow& w, int v) { return expf((w.lg[v] - w.mx) * w.inv_T) * w.inv_z; }
-__device__ inline float r_weight(const SampleRow& w, int v, float q) { return fmaxf(0.f, q * w.inv_beta - w.p[v]); }
-
 // Inclusive scan of one fp64 value over the 64 lanes of a wave.
 __device__ inline double wave_scan(double x, int lane) {
   for (int d = 1; d < 64; d <<= 1) {
@@ -744,18 +740,52 @@ __device__ inline double wave_scan(double x, int lane) {
   return x;
 }
 
-// Thread sums of one slice (both weight kinds) into LDS.
+// Weights of a slice's ids, eight a thread at a time (row stride 9: no bank
+// conflicts): q, and for kind 2 the residual weight r.
+struct SliceWeights {
+  float q[kSampleThreads * 9], r[kSampleThreads * 9];
+};
+__device__ inline float q_weight(const SampleRow& w, float x) { return expf((x - w.mx) * w.inv_T) * w.inv_z; }
+__device__ inline float r_weight(const SampleRow& w, float q, float p) { return fmaxf(0.f, q * w.inv_beta - p); }
+
+// Thread sums of one slice (both weight kinds) into LDS; with probs, also the
+// ids' probabilities, weight * inv_sum, to probs[v].  Thread t sums the ids
+// [t * E, t * E + E) in order, but the work-group reads and weighs them side by
+// side: thread by thread the eight loads and stores of a wave went to 64 cache
+// lines each (sums and probabilities of 16 rows of 128256 ids: 12.3 -> 6.6 us,
+// 3.2 us of it the bytes at the copy rate).
+// Leaves the last eight ids a thread (all of them if E <= 8) in sw.
 __device__ inline void slice_thread_sums(const SampleRow& w, int kind, int V, const SampleGeom& g, int slice_id,
-                                         double* tq, double* tr) {
+                                         SliceWeights& sw, double* tq, double* tr, float* probs = nullptr,
+                                         float inv_sum = 0.f) {
   const int t = threadIdx.x;
-  const int lo = slice_id * g.slice + t * g.E;
+  const int id = t & 7, lo = slice_id * g.slice + (t >> 3) * g.E + id;
   double sq = 0.0, sr = 0.0;
-  for (int e = 0; e < g.E; ++e) {
-    const int v = lo + e;
-    if (v >= V) break;
-    const float q = q_weight(w, v);
-    sq += (double)q;
-    if (kind == 2) sr += (double)r_weight(w, v, q);
+  for (int e = 0; e < g.E; e += 8) {
+    float x[8], p[8];
+    bool in[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int v = lo + i * (kSampleThreads / 8) * g.E + e;
+      in[i] = id + e < g.E && v < V;
+      x[i] = in[i] ? w.lg[v] : 0.f;
+      if (kind == 2) p[i] = in[i] ? w.p[v] : 0.f;
+    }
+    if (e) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float q = in[i] ? q_weight(w, x[i]) : 0.f;
+      const int o = (i * (kSampleThreads / 8) + (t >> 3)) * 9 + id;
+      sw.q[o] = q;
+      if (kind == 2) sw.r[o] = in[i] ? r_weight(w, q, p[i]) : 0.f;
+      if (probs && in[i]) probs[lo + i * (kSampleThreads / 8) * g.E + e] = q * inv_sum;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      sq += (double)sw.q[t * 9 + i];
+      if (kind == 2) sr += (double)sw.r[t * 9 + i];
+    }
   }
   tq[t] = sq;
   tr[t] = sr;
@@ -768,14 +798,29 @@ __device__ inline double lane_scan(const double* ts, int lane, double* lane_sum)
   return wave_scan(x, lane);
 }
 
-__global__ __launch_bounds__(kSampleThreads) void sample_sums_kernel(DecideArgs a) {
+// Requests: in device memory, or (kStaticSampleRows at most) in the kernel's arguments.
+struct ReqArray {
+  const SampleReq* r;
+};
+struct ReqArgs {
+  SampleReq r[kStaticSampleRows];
+};
+
+// Slice sums of every request; with probs, also request b's softmax
+// exp((l - max) / T) / sum as probs[b * ld + v], from the same loads.
+template <typename R>
+__global__ __launch_bounds__(kSampleThreads) void sample_sums_kernel(DecideArgs a, R req, float* probs, int ld) {
   const int b = blockIdx.y, g = blockIdx.x;
-  const SampleReq r = a.req[b];
+  const SampleReq r = req.r[b];
   if (r.kind == 0) return;  // uniform per work-group
   const SampleGeom geo = sample_geom(a.vocab);
   __shared__ double tq[kSampleThreads], tr[kSampleThreads];
+  __shared__ SliceWeights sw;
   const SampleRow w = sample_row(a, r, b);
-  slice_thread_sums(w, r.kind, a.vocab, geo, g, tq, tr);
+  if (probs)
+    slice_thread_sums(w, r.kind, a.vocab, geo, g, sw, tq, tr, probs + (size_t)b * ld, 1.f / a.s_row_sumexp[r.out]);
+  else
+    slice_thread_sums(w, r.kind, a.vocab, geo, g, sw, tq, tr);
   __syncthreads();
   if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
@@ -789,15 +834,17 @@ __global__ __launch_bounds__(kSampleThreads) void sample_sums_kernel(DecideArgs 
   }
 }
 
-__global__ __launch_bounds__(kSampleThreads) void sample_pick_kernel(DecideArgs a) {
+template <typename R>
+__global__ __launch_bounds__(kSampleThreads) void sample_pick_kernel(DecideArgs a, R req) {
   const int b = blockIdx.x;
-  const SampleReq r = a.req[b];
+  const SampleReq r = req.r[b];
   if (r.kind == 0) return;  // uniform per work-group
   const int V = a.vocab;
   const SampleGeom geo = sample_geom(V);
   const SampleRow w = sample_row(a, r, b);
   const int t = threadIdx.x, lane = t & 63;
   __shared__ double tq[kSampleThreads], tr[kSampleThreads];
+  __shared__ SliceWeights sw;
   __shared__ int s_slice, s_last, s_resid;
   __shared__ double s_acc, s_target;
   if (t < 64) {
@@ -834,7 +881,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_pick_kernel(DecideArgs 
   __syncthreads();
   const int c = s_slice;
   const bool resid = s_resid != 0;
-  slice_thread_sums(w, resid ? 2 : 1, V, geo, c, tq, tr);
+  slice_thread_sums(w, resid ? 2 : 1, V, geo, c, sw, tq, tr);
   __syncthreads();
   if (t >= 64) return;
   const double* ts = resid ? tr : tq;
@@ -874,13 +921,17 @@ __global__ __launch_bounds__(kSampleThreads) void sample_pick_kernel(DecideArgs 
         break;
       }
   }
-  const int lo = c * geo.slice + th * geo.E;
+  const int lo = c * geo.slice + th * geo.E, hi = min(lo + geo.E, V);
+  const float* wts = (resid ? sw.r : sw.q) + th * 9;  // these ids' weights, if E <= 8
   int tok = -1, lastpos = lo < V ? lo : V - 1;
-  for (int e = 0; e < geo.E; ++e) {
-    const int v = lo + e;
-    if (v >= V) break;
-    const float q = q_weight(w, v);
-    const float wt = resid ? r_weight(w, v, q) : q;
+  for (int v = lo; v < hi; ++v) {
+    float wt;
+    if (geo.E <= 8) {
+      wt = wts[v - lo];
+    } else {
+      wt = q_weight(w, w.lg[v]);
+      if (resid) wt = r_weight(w, wt, w.p[v]);
+    }
     if (wt > 0.f) {
       lastpos = v;
       run += (double)wt;
@@ -897,56 +948,44 @@ __global__ __launch_bounds__(kSampleThreads) void sample_pick_kernel(DecideArgs 
     a.packed[2 * a.batch + b] = drawn;
 }
 
-// probs[i * ld + v] = exp((l - max) / T) / sum for request i's row.
-__global__ __launch_bounds__(kSampleThreads) void sample_probs_kernel(DecideArgs a, float* probs, int ld) {
-  const int i = blockIdx.y;
-  const SampleReq r = a.req[i];
-  const SampleGeom geo = sample_geom(a.vocab);
-  const float* lg = a.s_logits + (size_t)r.out * a.vocab;
-  const float mx = a.s_row_max[r.out], inv_z = 1.f / a.s_row_sumexp[r.out];
-  float* o = probs + (size_t)i * ld;
-  const int lo = blockIdx.x * geo.slice;
-  const int hi = min(a.vocab, lo + geo.slice);
-  for (int v = lo + threadIdx.x; v < hi; v += kSampleThreads) o[v] = expf((lg[v] - mx) * a.inv_T) * inv_z;
-}
-
 }  // namespace
+
+template <typename R>
+static void launch_draws(const DecideArgs& a, const R& req, float* probs, int probs_ld, hipStream_t s) {
+  const SampleGeom g = sample_geom(a.vocab);
+  hipLaunchKernelGGL(sample_sums_kernel<R>, dim3(g.G, a.batch), dim3(kSampleThreads), 0, s, a, req, probs, probs_ld);
+  hipLaunchKernelGGL(sample_pick_kernel<R>, dim3(a.batch), dim3(kSampleThreads), 0, s, a, req);
+}
 
 void launch_decide(const DecideArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(decide_kernel, dim3(a.batch), dim3(64), 0, s, a);
-  if (a.draft_probs) {
-    const SampleGeom g = sample_geom(a.vocab);
-    hipLaunchKernelGGL(sample_sums_kernel, dim3(g.G, a.batch), dim3(kSampleThreads), 0, s, a);
-    hipLaunchKernelGGL(sample_pick_kernel, dim3(a.batch), dim3(kSampleThreads), 0, s, a);
-  }
+  if (a.draft_probs) launch_draws(a, ReqArray{a.req}, nullptr, 0, s);
 }
 
-void launch_sample_rows(const DecideArgs& a, float* probs, int probs_ld, hipStream_t s) {
+// Probabilities that may lie over the logits (n_logits floats) go out after
+// the pick has read those; otherwise with the sums, which saves a launch.
+template <typename R>
+static void launch_rows(const DecideArgs& a, const R& req, size_t n_logits, float* probs, int probs_ld, hipStream_t s) {
+  const uintptr_t p = (uintptr_t)probs, l = (uintptr_t)a.s_logits;
+  const bool over = probs && p < l + n_logits * 4 && l < p + ((size_t)(a.batch - 1) * probs_ld + a.vocab) * 4;
+  launch_draws(a, req, over ? nullptr : probs, probs_ld, s);
+  if (!over) return;
   const SampleGeom g = sample_geom(a.vocab);
-  hipLaunchKernelGGL(sample_sums_kernel, dim3(g.G, a.batch), dim3(kSampleThreads), 0, s, a);
-  hipLaunchKernelGGL(sample_pick_kernel, dim3(a.batch), dim3(kSampleThreads), 0, s, a);
-  if (probs) hipLaunchKernelGGL(sample_probs_kernel, dim3(g.G, a.batch), dim3(kSampleThreads), 0, s, a, probs, probs_ld);
+  hipLaunchKernelGGL(sample_sums_kernel<R>, dim3(g.G, a.batch), dim3(kSampleThreads), 0, s, a, req, probs, probs_ld);
+}
+
+void launch_sample_rows(const DecideArgs& a, int out_rows, float* probs, int probs_ld, hipStream_t s) {
+  launch_rows(a, ReqArray{a.req}, (size_t)out_rows * a.vocab, probs, probs_ld, s);
 }
 
 // ---------------------------------------------------------------- draws without allocation
 // Scratch of the draw entry point that allocates nothing (via_sample_rows_static):
-// the request array, then the per-slice sums [request][slice][2].  Each GPU
-// holds its own copy until the process ends; every call on a GPU reuses it.
+// the per-slice sums [request][slice][2] (the requests are kernel arguments).
+// Each GPU holds its own copy until the process ends; every call on a GPU reuses it.
 namespace {
-constexpr size_t kStaticReqBytes = (size_t)kStaticSampleRows * sizeof(SampleReq);
-constexpr size_t kStaticScratchBytes = kStaticReqBytes + (size_t)kStaticSampleRows * kSampleSlices * 2 * sizeof(double);
-static_assert(kStaticScratchBytes == 66560, "the size include/via.h states");
+constexpr size_t kStaticScratchBytes = (size_t)kStaticSampleRows * kSampleSlices * 2 * sizeof(double);
+static_assert(kStaticScratchBytes == 65536, "the size include/via.h states");
 static __device__ __align__(256) char scratch[kStaticScratchBytes];
-
-// Requests travel as kernel arguments (no host buffer, no copy).
-struct StaticReqs {
-  SampleReq r[kStaticSampleRows];
-  int n;
-};
-__global__ __launch_bounds__(kStaticSampleRows) void put_reqs_kernel(StaticReqs q, SampleReq* dst) {
-  const int i = threadIdx.x;
-  if (i < q.n) dst[i] = q.r[i];
-}
 }  // namespace
 
 hipError_t static_scratch(void** ptr, size_t* bytes) {
@@ -969,17 +1008,13 @@ hipError_t static_scratch(void** ptr, size_t* bytes) {
   return hipSuccess;
 }
 
-void launch_sample_rows_static(DecideArgs a, const SampleReq* req, int n, void* scratch_ptr, float* probs,
-                               int probs_ld, hipStream_t s) {
-  StaticReqs q{};
+void launch_sample_rows_static(DecideArgs a, int out_rows, const SampleReq* req, int n, void* scratch_ptr,
+                               float* probs, int probs_ld, hipStream_t s) {
+  ReqArgs q{};
   for (int i = 0; i < n; ++i) q.r[i] = req[i];
-  q.n = n;
-  char* base = (char*)scratch_ptr;
-  a.req = (SampleReq*)base;
-  a.slice_sum = (double*)(base + kStaticReqBytes);
+  a.slice_sum = (double*)scratch_ptr;
   a.batch = n;
-  hipLaunchKernelGGL(put_reqs_kernel, dim3(1), dim3(kStaticSampleRows), 0, s, q, a.req);
-  launch_sample_rows(a, probs, probs_ld, s);
+  launch_rows(a, q, (size_t)out_rows * a.vocab, probs, probs_ld, s);
 }
 
 void launch_kv_moves(bool bf16, void* pool, int pool_blocks, int n_slots, int KVH, int hd, const int32_t* btab,

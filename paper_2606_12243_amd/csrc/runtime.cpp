@@ -1179,7 +1179,7 @@ via_status via_sample_rows(via_kv* kv, const via_verify_out* out, int32_t out_ro
   a.req = (SampleReq*)(kv->ws + L.sreq);
   a.slice_sum = (double*)(kv->ws + L.ssum);
   a.tok_out = tokens;
-  launch_sample_rows(a, probs, probs_ld, s);
+  launch_sample_rows(a, out_rows, probs, probs_ld, s);
   return hip_check(kv, hipGetLastError(), "sample launch");
 }
 
@@ -1271,7 +1271,7 @@ via_status via_sample_rows_static(const via_verify_out* out, int32_t out_rows, i
   a.beta = 1.f;
   a.vocab = vocab;
   a.tok_out = tokens;
-  launch_sample_rows_static(a, req.data(), n, scr, probs, probs_ld, (hipStream_t)stream);
+  launch_sample_rows_static(a, out_rows, req.data(), n, scr, probs, probs_ld, (hipStream_t)stream);
   e = hipGetLastError();
   if (e != hipSuccess) return fail(VIA_EDEVICE, "sample launch: %s", hipGetErrorString(e));
   return VIA_OK;
