@@ -411,7 +411,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnArgs a) {
 // online softmax: a wave per query; P V: thread = (dim, share of the pages),
 // accumulating every query in registers.  The serial form it replaces (a wave
 // per query walking the keys one by one, a cross-lane sum each) took 30 us at
-// 36 keys, latency all of it; this takes 5.
+// 36 keys, latency all of it; this takes 13.
 template <int HD>
 __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
   constexpr int kKeys = 256, kParts = 256 / HD, kQ = kAttnQueries;
@@ -425,10 +425,23 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
   __shared__ float m_s[kQ], l_s[kQ], al_s[kQ];
   __shared__ int vis_s[kQ];
   __shared__ uint64_t mask_s[kQ];
-  for (int e = tid; e < nq * HD; e += 256) {
-    const int q = e / HD, i = e - q * HD, rl = (it.q0 + q) / G;
+  const int d = tid % HD, part = tid / HD;
+  // page of the thread's key (past the end: the last key again, masked below)
+  // and V of its share's first page, loaded a block ahead
+  float v[kBlock];
+  auto k_page = [&](int kb) { return a.btab[it.bt + min(kb + tid, it.kv_len - 1) / kBlock]; };
+  auto v_page = [&](int kb, int p) { return a.btab[it.bt + min(kb / kBlock + p, (it.kv_len - 1) / kBlock)]; };
+  auto load_v = [&](int page) {
+    const float* vp = pool + v_off(a.layer_slot, page, a.pool_blocks, a.KVH, HD, g, 0, d);
+#pragma unroll
+    for (int t = 0; t < kBlock; t += 4) *(float4*)&v[t] = *(const float4*)(vp + t);
+  };
+  int kpage = k_page(0);
+  const int vpage = v_page(0, part);
+  for (int e = tid; e < nq * (HD / 4); e += 256) {
+    const int q = e / (HD / 4), i = e - q * (HD / 4), rl = (it.q0 + q) / G;
     const int head = g * G + (it.q0 + q - rl * G);
-    q_s[q][i] = ((const float*)a.q_hi)[((size_t)(it.row_start + rl) * a.H + head) * HD + i];
+    *(float4*)&q_s[q][i * 4] = *(const float4*)((const float*)a.q_hi + ((size_t)(it.row_start + rl) * a.H + head) * HD + i * 4);
   }
   if (tid < nq) {
     const RowInfo ri = a.rows[it.row_start + (it.q0 + tid) / G];
@@ -437,18 +450,18 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     m_s[tid] = -INFINITY;
     l_s[tid] = 0.f;
   }
+  load_v(vpage);
   __syncthreads();
   int min_vis = it.kv_len;
   for (int q = 0; q < nq; ++q) min_vis = min(min_vis, vis_s[q]);
-  const int d = tid % HD, part = tid / HD;
   float o[kQ];
 #pragma unroll
   for (int q = 0; q < kQ; ++q) o[q] = 0.f;
   for (int kb = 0; kb < it.kv_len; kb += kKeys) {
     const bool all_visible = kb + kKeys <= min_vis;  // uniform
     {
-      const int key = min(kb + tid, it.kv_len - 1);  // past the end: the last key again, masked below
-      const float* kp = pool + k_off(a.layer_slot, a.btab[it.bt + key / kBlock], a.pool_blocks, a.KVH, HD, g, key % kBlock, 0);
+      const int tok = min(kb + tid, it.kv_len - 1) % kBlock;
+      const float* kp = pool + k_off(a.layer_slot, kpage, a.pool_blocks, a.KVH, HD, g, tok, 0);
       for (int q0 = 0; q0 < nq; q0 += 8) {
         float s[8];
 #pragma unroll
@@ -480,19 +493,21 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
           }
       }
     }
+    const bool more = kb + kKeys < it.kv_len;
+    if (more) kpage = k_page(kb + kKeys);
     __syncthreads();
     for (int q = wave; q < nq; q += 4) {
-      float v[kKeys / 64], mx = -INFINITY;
+      float x[kKeys / 64], mx = -INFINITY;
 #pragma unroll
       for (int i = 0; i < kKeys / 64; ++i) {
-        v[i] = p_s[q][i * 64 + lane];
-        mx = fmaxf(mx, v[i]);
+        x[i] = p_s[q][i * 64 + lane];
+        mx = fmaxf(mx, x[i]);
       }
       const float m_old = m_s[q], m_new = fmaxf(m_old, wave_max(mx));
       float sum = 0.f;
 #pragma unroll
       for (int i = 0; i < kKeys / 64; ++i) {
-        const float p = v[i] == -INFINITY ? 0.f : expf(v[i] - m_new);  // NaN scores stay NaN
+        const float p = x[i] == -INFINITY ? 0.f : expf(x[i] - m_new);  // NaN scores stay NaN
         p_s[q][i * 64 + lane] = p;
         sum += p;
       }
@@ -510,10 +525,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
       if (q < nq) o[q] *= al_s[q];
     const int np = (min(kKeys, it.kv_len - kb) + kBlock - 1) / kBlock;
     for (int p = part; p < np; p += kParts) {
-      const float* vp = pool + v_off(a.layer_slot, a.btab[it.bt + kb / kBlock + p], a.pool_blocks, a.KVH, HD, g, 0, d);
-      float v[kBlock];
-#pragma unroll
-      for (int t = 0; t < kBlock; t += 4) *(float4*)&v[t] = *(const float4*)(vp + t);
+      if (p != part) load_v(v_page(kb, p));
       if (all_visible) {
 #pragma unroll
         for (int q = 0; q < kQ; ++q)
@@ -538,34 +550,28 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
             }
       }
     }
+    if (more) load_v(v_page(kb + kKeys, part));
     __syncthreads();  // the scores' buffer is free again
   }
-  // sum of the page shares (in order), scaled by 1 / l, through the scores' buffer
-  float* r_s = &p_s[0][0];  // [part][q][HD] would exceed it at 32 queries: one share at a time
-  for (int s = 1; s < kParts; ++s) {
-    if (part == s)
+  // the page shares, summed in order and divided by l, through the scores' buffer
+  static_assert(kParts * HD == kKeys, "all shares fit the scores' buffer");
+  float* r_s = &p_s[0][0];  // [part][q][HD]
 #pragma unroll
-      for (int q = 0; q < kQ; ++q)
-        if (q < nq) r_s[q * HD + d] = o[q];
-    __syncthreads();
-    if (part == 0)
-#pragma unroll
-      for (int q = 0; q < kQ; ++q)
-        if (q < nq) o[q] += r_s[q * HD + d];
-    __syncthreads();
-  }
-  if (part == 0)
-#pragma unroll
-    for (int q = 0; q < kQ; ++q)
-      if (q < nq) r_s[q * HD + d] = o[q] / l_s[q];
+  for (int q = 0; q < kQ; ++q)
+    if (q < nq) r_s[(part * kQ + q) * HD + d] = o[q];
   __syncthreads();
   for (int e = tid; e < nq * (HD / 8); e += 256) {
     const int q = e / (HD / 8), i = e - q * (HD / 8), rl = (it.q0 + q) / G;
     const int head = g * G + (it.q0 + q - rl * G);
-    float v[8];
+    float x[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = r_s[q * HD + i * 8 + c];
-    put_afrag<false, 1>(a.out, it.row_start + rl, head * HD + i * 8, v, (a.H * HD) >> 5, a.MBn);
+    for (int c = 0; c < 8; ++c) {
+      x[c] = r_s[q * HD + i * 8 + c];
+#pragma unroll
+      for (int s = 1; s < kParts; ++s) x[c] += r_s[(s * kQ + q) * HD + i * 8 + c];
+      x[c] /= l_s[q];
+    }
+    put_afrag<false, 1>(a.out, it.row_start + rl, head * HD + i * 8, x, (a.H * HD) >> 5, a.MBn);
   }
 }
 
