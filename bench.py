@@ -546,7 +546,7 @@ def measured_copy_gbs(nbytes=1 << 30, reps=5):
 
 
 def prefill_gemm_roofline(md, M, reps=10):
-    """The prefill GEMM (the tile kernel of forwards of more than 512 rows) on
+    """The prefill GEMM (the tile kernel of prefill-sized forwards) on
     plain bf16 operands at the model's four projection shapes with M prefill
     rows: algorithmic 2 M N K flops per launch / the average launch time (HIP
     events on the stream of the call) against the bf16 MFMA peak.  The four

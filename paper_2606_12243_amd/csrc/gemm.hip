@@ -204,7 +204,7 @@ __device__ __forceinline__ void merge3(float& mx, int& am, float& sc, float mx2,
 // max, argmax), the logit of each draft token inside the tile, and the
 // optional fp32 logits dump.  16 threads per row take every 16th column (no
 // bank conflicts) and leave the scaled logits in the tile; the dump is written
-// a row per wave, 256 contiguous bytes a store (8B, 256 rows: 590 -> 480 us).
+// a row per wave, 256 contiguous bytes a store (8B, 256 rows: 590 -> 470 us).
 template <int MB, int TN = kTileN, int LDC = TN, int THR = kThreads>
 __device__ void epi_stats(const GemmArgs& a, int tile, int m0, float* lds) {
   const int grp = threadIdx.x >> 4, gl = threadIdx.x & 15;  // THR / 16 groups of 16 threads
@@ -417,8 +417,8 @@ __global__ __launch_bounds__(kThreads) void gemm_f32(GemmArgs a) {
 // main loop), one step of loads ahead of its MFMAs.  Weights are read with
 // non-temporal loads: streamed once, they should not displace X from the
 // caches.  The eight waves' partial tiles are summed in LDS in wave order
-// (fixed, so the result is reproducible) and the epilogue writes h as in
-// gemm_gate_up.
+// (fixed, so the result is reproducible) and the epilogue writes h as the
+// down projection's fragments.
 __device__ __forceinline__ uint4 load_stream(const uint4* p) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
@@ -561,7 +561,7 @@ void launch_f32(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, 
 // and weights with non-temporal loads, one step ahead.  The 8 wave partial
 // tiles are summed in LDS in wave order and written to
 // a.part[split][M][N], which the consumer sums in split order.  Fewer,
-// longer splits than the LDS-staged kernels write a quarter of the partials.
+// longer splits (4-8, not 10-16) write a quarter of the partials.
 template <int MB, int NT>
 __global__ __launch_bounds__(kThreads) void gemm_ki_part(GemmArgs a) {
   constexpr int NBM = kWaves;
@@ -1047,7 +1047,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_prefill(GemmArgs a, int nt) 
 // bytes per product.
 //
 // kPart writes one fp32 partial per split, kSwiglu (the gate/up projection)
-// writes h as in gemm_gate_up, kStats the head's row statistics.
+// writes h as the down projection's fragments, kStats the head's row statistics.
 // Tile and K splits of one projection.
 struct RtPlan {
   int rows, cols, ks;
