@@ -39,7 +39,6 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 constexpr int kNBW = 2;                // 16-column blocks per wave
 constexpr int kTileN = 8 * 16 * kNBW;   // columns per work-group tile (8 waves)
-int gemm_tiles(int N) { return (N + kTileN - 1) / kTileN; }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -522,7 +521,7 @@ void launch_timed(K kernel, dim3 grid, int threads, const GemmArgs& a, hipStream
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a);
 }
 void launch_head(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const dim3 grid(gemm_tiles(a.N));
+  const dim3 grid(gemm_head_tiles(true, a.M, a.N, a.K));
   if (a.M <= 16)
     launch_timed(gemm_head<1, 4>, grid, kThreads, a, s, e0, e1);
   else
@@ -535,7 +534,6 @@ void launch_gate_up_ki(const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
   else
     launch_timed(gemm_gate_up_ki<2>, grid, kThreads, a, s, e0, e1);
 }
-constexpr int kF32HeadCols = 64;  // columns of an fp32 head tile
 void launch_f32(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   // one 16-row block as far as it goes, else 64 rows; one column block per
   // work-group until there are 256 of them with four
@@ -843,7 +841,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const T* src, T* dst, int row
 // rows of the same 8 FFN indices, so lane n < 8 of an output block takes its
 // up value from lane n + 8; h of the tile's 128 FFN indices is staged in LDS
 // (the freed operand stages) and written 8 indices per fragment group.
-constexpr int kPfBM = 256, kPfBN = 256, kPfStages = 4, kPfStage = 32 * 1024;
+constexpr int kPfStages = 4, kPfStage = 32 * 1024;
 constexpr int kPfGroupM = 8;
 constexpr int kPfHStride = kPfBN / 2 + 4;  // fp32 per staged h row (padded: no bank conflicts)
 constexpr int kPfLds = kPfStages * kPfStage > kPfBM * kPfHStride * 4 ? kPfStages * kPfStage : kPfBM * kPfHStride * 4;
@@ -1048,34 +1046,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_prefill(GemmArgs a, int nt) 
 //
 // kPart writes one fp32 partial per split, kSwiglu (the gate/up projection)
 // writes h as the down projection's fragments, kStats the head's row statistics.
-// Tile and K splits of one projection.
-struct RtPlan {
-  int rows, cols, ks;
-  double us;  // estimate
-};
-// The tile and split with the smallest estimate: rounds of tiles on 256 compute
-// units, and every split's partial written and read back at ~3 TB/s.  The time
-// of a round per 4096 of K is measured on the 8B gate/up projection (48, 96,
-// 128, 160 and 256 rows).  Above kFixedOrderRows rows there is one split and one
-// order of summation (that of the prefill tiles too), whatever the row count.
-RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
-  struct Tile {
-    int rows, cols;
-    double us;
-  };
-  static constexpr Tile kTiles[] = {{64, 128, 48.0}, {96, 128, 53.0}, {128, 128, 64.0}, {96, 256, 74.0}, {128, 256, 92.0}};
-  const bool split = role != GemmRole::kGateUp && role != GemmRole::kHead && M <= kFixedOrderRows;
-  RtPlan best{0, 0, 0, 0.0};
-  for (const Tile& tl : kTiles) {
-    if (M > kFixedOrderRows && tl.cols == 128) continue;  // its two K halves are another order
-    const int tiles = ((M + tl.rows - 1) / tl.rows) * ((N + tl.cols - 1) / tl.cols);
-    for (int ks = 1; ks <= (split ? 8 : 1) && (ks == 1 || K / 32 >= 16 * ks); ks *= 2) {
-      const double us = 10.0 + tl.us * ((tiles * ks + 255) / 256) * K / (4096.0 * ks) + 8e-6 / 3.0 * ks * M * (double)N;
-      if (!best.ks || us < best.us) best = RtPlan{tl.rows, tl.cols, ks, us};
-    }
-  }
-  return best;
-}
 // s_waitcnt operand: at most vm vector-memory and lgkm LDS operations outstanding
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | ((vm >> 4) << 14); }
 
@@ -1349,49 +1319,6 @@ void launch_pack(bool bf16, const void* src, void* dst, int rows, int cols, int 
   else
     hipLaunchKernelGGL(pack_kernel<float>, grid, dim3(256), 0, s, (const float*)src, (float*)dst, rows, cols, ffn,
                        groups);
-}
-
-int gate_up_blocks_per_group(int F) {
-  const int nblocks = F / 8;  // 2 F columns in blocks of 16
-  return std::max(1, std::min(kWaves, (nblocks + 255) / 256));
-}
-
-GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K) {
-  if (!bf16) return GemmPath::kF32;
-  if (M <= 32) return role == GemmRole::kHead ? GemmPath::kHead : GemmPath::kStream;
-  if (M <= 128 || role == GemmRole::kHead) return GemmPath::kRowTile;
-  // 256 x 256 tiles take 178 us a round per 4096 of K, less than the two rounds
-  // of row tiles they stand for, when there are enough of them
-  const int tiles = ((M + kPfBM - 1) / kPfBM) * ((N + kPfBN - 1) / kPfBN);
-  const double us = 20.0 + 178.0 * ((tiles + 255) / 256) * K / 4096.0 + 8e-6 / 3.0 * M * (double)N;
-  return us < row_tile_plan(role, M, N, K).us ? GemmPath::kPrefill : GemmPath::kRowTile;
-}
-
-int gemm_splits(GemmRole role, int M, int N, int K) { return row_tile_plan(role, M, N, K).ks; }
-
-int gemm_head_tiles(bool bf16, int M, int N, int K) {
-  if (gemm_path(bf16, GemmRole::kHead, M, N, K) == GemmPath::kHead) return gemm_tiles(N);
-  const int cols = bf16 ? row_tile_plan(GemmRole::kHead, M, N, K).cols : kF32HeadCols;
-  return (N + cols - 1) / cols;
-}
-
-void gemm_ki_plan(int N, int K, int* nb, int* ksplit) {
-  const int S = K / 32, blocks = N / 16;
-  // at least 4 steps per wave in a split; long K (the down projection) in 8
-  // splits, which with 8 blocks per work-group halves the activation reads
-  // per weight byte and keeps the grid at one round
-  const int ks = S >= 256 ? 8 : std::max(1, std::min(4, S / 32));
-  *ksplit = ks;
-  *nb = std::max(1, std::min(kWaves, (blocks * ks + 255) / 256));
-}
-
-int gemm_rows_per_group(int M) {
-  return M > 96 ? 128 : M > 64 ? 96 : M > 48 ? 64 : M > 32 ? 48 : M > 16 ? 32 : 16;
-}
-
-int gemm_padded_rows(int M) {
-  const int g = gemm_rows_per_group(M);
-  return (M + g - 1) / g * g;
 }
 
 void launch_gemm(bool bf16, GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {

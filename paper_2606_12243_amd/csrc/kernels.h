@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "gemm_plan.h"
 
 namespace via {
 
@@ -34,56 +35,22 @@ struct GemmArgs {
   float eps;
 };
 
-// Projection a GEMM computes: the head reduces its tiles to row statistics
-// instead of writing partials; the gate/up projection runs over all of K and
-// applies SwiGLU itself.
-enum class GemmRole { kQkv, kO, kGateUp, kDown, kHead };
 // bf16 terms per fp32 activation at every projection's input (bf16 models).
 constexpr int kTerms = 2;
 // e0/e1 (both or neither): timing events recorded at the kernel's own start
 // and end.
 void launch_gemm(bool bf16, GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                  hipEvent_t e1 = nullptr);
-// Kernel family of an [M, K] x [N, K]^T projection.
-//   kStream   bf16, up to 32 rows: weights stream past registers; QKV, O and
-//             down in work-groups of a.nb 16-column blocks of one of a.ksplit
-//             K splits (gemm_ki_plan), gate/up over all of K
-//   kRowTile  bf16, 33 rows and more (the head's only kernel there): LDS-fed
-//             tiles of 64 to 128 rows x 128 or 256 columns, gemm_splits K splits
-//   kPrefill  bf16, enough rows to fill the GPU with 256 x 256 tiles (one partial)
-//   kHead     the bf16 head of up to 32 rows
-//   kF32      every projection and size of fp32 models (one partial)
-enum class GemmPath { kStream, kRowTile, kPrefill, kHead, kF32 };
-GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K);
-// K splits (partial products) of the kRowTile kernel.
-int gemm_splits(GemmRole role, int M, int N, int K);
-// Forwards of more rows than this sum every projection in one order, so that a
-// row's result does not depend on the rows it is batched with.
-constexpr int kFixedOrderRows = 2048;
 // Forwards of more rows than this take the many-row forms of the residual
 // update and the QKV finish.
 constexpr int kManyRows = 512;
-// Column tiles the head of M rows reduces its statistics to.
-int gemm_head_tiles(bool bf16, int M, int N, int K);
 // Plain bf16 product a.part[M, N] = X[M, K] W[N, K]^T (one activation term)
 // on the prefill GEMM.
 void launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
-// Blocks per work-group and K splits of the kStream kernels for an [N, K]
-// weight (about 256 work-groups).
-void gemm_ki_plan(int N, int K, int* nb, int* ksplit);
-// Rows per GEMM work-group for M rows (16, 32, 48, 64, 96 or 128).
-int gemm_rows_per_group(int M);
-// Rows of the activation fragments for M rows: M padded to a multiple of
-// gemm_rows_per_group(M); non-decreasing in M.
-int gemm_padded_rows(int M);
 // Row-major [rows, cols] -> packed weight tiles (see include/via.h).  With
 // ffn > 0 the source is [2 ffn, cols] (gate rows, then up rows) and packed
 // row 16 b + i takes gate row 8 b + i (i < 8) or up row 8 b + i - 8.
 void launch_pack(bool bf16, const void* src, void* dst, int rows, int cols, int ffn, hipStream_t s);
-// 16-column blocks per gate/up work-group for d_ffn = F (1..8, about one
-// work-group per compute unit).
-int gate_up_blocks_per_group(int F);
-
 // X[m] += sum_s P[s][m] (split order; P may be null); x * g is written as
 // activation fragments (kTerms bf16 terms, or fp32), to fragment row
 // rows[m].lm when `rows` is given (rows with lm < 0 skipped), and the sums of

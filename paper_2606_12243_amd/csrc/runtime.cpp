@@ -26,21 +26,6 @@ size_t al(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 int esize_of(const via_model_desc* d) { return d->dtype == VIA_DTYPE_BF16 ? 2 : 4; }
 
-struct GemmShape {
-  int N, K;
-  GemmRole role;
-  int nb_ki, ks_ki;  // the K-interleaved kernel's blocks per work-group and splits (forwards of <= 32 rows)
-
-  // K splits of a forward of M rows
-  int splits(bool bf16, int M) const {
-    switch (gemm_path(bf16, role, M, N, K)) {
-      case GemmPath::kStream: return ks_ki;
-      case GemmPath::kRowTile: return gemm_splits(role, M, N, K);
-      default: return 1;
-    }
-  }
-};
-
 struct Dims {
   int L, d, H, KVH, hd, F, V, qkv, G;
   GemmShape g_qkv, g_o, g_gu, g_down;
@@ -57,16 +42,10 @@ Dims dims_of(const via_model_desc* d) {
   r.V = d->vocab;
   r.qkv = (r.H + 2 * r.KVH) * r.hd;
   r.G = r.H / std::max(1, r.KVH);
-  const bool f32 = d->dtype != VIA_DTYPE_BF16;
-  auto shape = [&](int N, int K, GemmRole role) {
-    GemmShape g{N, K, role, 1, 1};
-    gemm_ki_plan(N, K, &g.nb_ki, &g.ks_ki);
-    return g;
-  };
-  r.g_qkv = shape(r.qkv, r.d, GemmRole::kQkv);
-  r.g_o = shape(r.d, r.H * r.hd, GemmRole::kO);
+  r.g_qkv = gemm_shape(GemmRole::kQkv, r.qkv, r.d);
+  r.g_o = gemm_shape(GemmRole::kO, r.d, r.H * r.hd);
   r.g_gu = GemmShape{2 * r.F, r.d, GemmRole::kGateUp, 1, 1};  // full K per work-group (SwiGLU epilogue)
-  r.g_down = shape(r.d, r.F, GemmRole::kDown);
+  r.g_down = gemm_shape(GemmRole::kDown, r.d, r.F);
   return r;
 }
 
@@ -104,18 +83,10 @@ Layout layout_of(const via_model_desc* desc, int max_rows, int max_batch, int ma
   L.Af = take(Rp * D.H * D.hd * f2);
   L.Hf = take(Rp * D.F * f2);
   L.Ylf = take(Rp * D.d * f2);
-  // split-K partials: the most any forward of up to max_rows rows writes.  The
-  // splits depend on the rows only through the row tiles, so the last row
-  // count of each tile count is enough.  The gate/up kernels write h directly
-  // and need none.
-  size_t part = 0;
-  for (const GemmShape& g : {D.g_qkv, D.g_o, D.g_down})
-    for (size_t M = 32;; M += 32) {
-      const size_t m = std::min(M, R);
-      part = std::max(part, (size_t)g.splits(es == 2, (int)m) * m * g.N * 4);
-      if (M >= R) break;
-    }
-  L.part = take(part);
+  // split-K partials: the most any forward of up to max_rows rows writes (the
+  // gate/up kernels write h directly and need none)
+  const GemmShape projections[] = {D.g_qkv, D.g_o, D.g_down};
+  L.part = take(gemm_part_floats(es == 2, projections, 3, max_rows) * 4);
   L.max_chunks = std::min(kAttnMaxSplits, ceil_div(max_blocks * kBlock, 32));
   L.att_o = take((size_t)L.max_chunks * R * D.H * D.hd * 4);
   L.att_ml = take((size_t)L.max_chunks * R * D.H * 2 * 4);

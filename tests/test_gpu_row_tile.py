@@ -30,22 +30,31 @@ SPLIT = dict(name="split_k", seed_w=21, seed_c=22, route=[0],
                         dtype="bf16", rms_eps=1e-5, rope_theta=10000.0))
 
 
+# one layer of the 8B and the 1B widths (narrow FFN and vocabulary where they do not matter)
+WIDE = {
+    "width_8b": dict(name="width_8b", seed_w=31, seed_c=32, route=[0],
+                     model=dict(n_layers=1, d_model=4096, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=512, vocab=700,
+                                dtype="bf16", rms_eps=1e-5, rope_theta=10000.0)),
+    "width_1b": dict(name="width_1b", seed_w=33, seed_c=34, route=[0],
+                     model=dict(n_layers=1, d_model=2048, n_heads=16, n_kv_heads=4, head_dim=128, d_ffn=5632, vocab=700,
+                                dtype="bf16", rms_eps=1e-5, rope_theta=10000.0)),
+}
+
+
 @functools.lru_cache(maxsize=None)
 def models(name):
-    cfg = SPLIT if name == "split_k" else dict(configs.get(name), seed_c=23)
+    cfg = SPLIT if name == "split_k" else WIDE[name] if name in WIDE else dict(configs.get(name), seed_c=23)
     W = gen.model_weights(cfg)
     return cfg, via.Model(cfg["model"], W, list(range(cfg["model"]["n_layers"]))), OracleModel(cfg["model"], W)
 
 
-@pytest.mark.parametrize("name,rows", [(n, r) for n in ("small_bf16_hd128", "split_k")
-                                       for r in (33, 64, 65, 96, 97, 128, 129, 192, 193, 300, 520)])
-def test_window_logits_match_oracle(name, rows):
-    print(f"[case] row tile {name} rows={rows}", flush=True)
+def check_window(name, rows, max_rows):
+    """A probe of `rows` rows on a handle for up to `max_rows`, against the oracle."""
     cfg, model, oracle = models(name)
     V = cfg["model"]["vocab"]
     tokens = gen.context_tokens(cfg, 0, rows)
     blocks = (rows + via.BLOCK - 1) // via.BLOCK
-    kv = via.KV(model, max_seqs=1, max_blocks_per_seq=blocks, blocks_full=blocks, blocks_slim=blocks, max_rows=rows,
+    kv = via.KV(model, max_seqs=1, max_blocks_per_seq=blocks, blocks_full=blocks, blocks_slim=blocks, max_rows=max_rows,
                 max_batch=1, max_drafts=1)
     try:
         via.check(via.via_kv_seq_reserve(kv.h, 0, 0))
@@ -65,3 +74,21 @@ def test_window_logits_match_oracle(name, rows):
         assert ((out.row_sumexp.cpu().double() - se).abs() / se).max().item() < 1e-5
     finally:
         kv.close()
+
+
+@pytest.mark.parametrize("name,rows", [(n, r) for n in ("small_bf16_hd128", "split_k")
+                                       for r in (33, 64, 65, 96, 97, 128, 129, 192, 193, 300, 520)])
+def test_window_logits_match_oracle(name, rows):
+    print(f"[case] row tile {name} rows={rows}", flush=True)
+    check_window(name, rows, rows)
+
+
+@pytest.mark.parametrize("name,rows,max_rows", [("width_8b", 33, 48), ("width_8b", 41, 48), ("width_8b", 41, 42),
+                                                ("width_1b", 225, 300), ("width_1b", 251, 252)])
+def test_forward_below_max_rows(name, rows, max_rows):
+    """A forward of fewer rows than its handle is for may split K further, and
+    its partial products then need more workspace than the largest forward's.
+    The cache is as short as the rows, so that the regions behind the partial
+    products (norm sums, rotations) are close."""
+    print(f"[case] {name} rows={rows} max_rows={max_rows}", flush=True)
+    check_window(name, rows, max_rows)
