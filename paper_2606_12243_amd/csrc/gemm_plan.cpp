@@ -10,12 +10,17 @@ constexpr int kGroupBlocks = 8;      // 16-column blocks of a kStream work-group
 constexpr int kHeadTileCols = 256;   // columns of a kHead tile
 constexpr int kF32HeadTileCols = 64;  // ... and of an fp32 head tile
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Time of an fp32 [M, N] partial, written and read back at ~3 TB/s.  Rows count
+// in blocks of 32, which every tile height is a multiple of: all row counts of a
+// block then get one plan, and a forward's sums do not change their order when
+// one row is added inside a block.
+double partial_us(int M, int N) { return 8e-6 / 3.0 * (ceil_div(M, 32) * 32) * (double)N; }
 }  // namespace
 
 // The tile and split with the smallest estimate: rounds of tiles on 256 compute
-// units, and every split's partial written and read back at ~3 TB/s.  The time
-// of a round per 4096 of K is measured on the 8B gate/up projection (48, 96,
-// 128, 160 and 256 rows).  Above kFixedOrderRows rows there is one split and one
+// units and every split's partial.  The time of a round per 4096 of K is measured
+// on the 8B gate/up projection (48, 96, 128, 160 and 256 rows).  Above kFixedOrderRows rows there is one split and one
 // order of summation (that of the prefill tiles too), whatever the row count.
 RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
   struct Tile {
@@ -29,7 +34,7 @@ RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
     if (M > kFixedOrderRows && tl.cols == 128) continue;  // its two K halves are another order
     const int tiles = ceil_div(M, tl.rows) * ceil_div(N, tl.cols);
     for (int ks = 1; ks <= (split ? 8 : 1) && (ks == 1 || K / 32 >= 16 * ks); ks *= 2) {
-      const double us = 10.0 + tl.us * ceil_div(tiles * ks, 256) * K / (4096.0 * ks) + 8e-6 / 3.0 * ks * M * (double)N;
+      const double us = 10.0 + tl.us * ceil_div(tiles * ks, 256) * K / (4096.0 * ks) + ks * partial_us(M, N);
       if (!best.ks || us < best.us) best = RtPlan{tl.rows, tl.cols, ks, us};
     }
   }
@@ -43,7 +48,7 @@ GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K) {
   // 256 x 256 tiles take 178 us a round per 4096 of K, less than the two rounds
   // of row tiles they stand for, when there are enough of them
   const int tiles = ceil_div(M, kPfBM) * ceil_div(N, kPfBN);
-  const double us = 20.0 + 178.0 * ceil_div(tiles, 256) * K / 4096.0 + 8e-6 / 3.0 * M * (double)N;
+  const double us = 20.0 + 178.0 * ceil_div(tiles, 256) * K / 4096.0 + partial_us(M, N);
   return us < row_tile_plan(role, M, N, K).us ? GemmPath::kPrefill : GemmPath::kRowTile;
 }
 

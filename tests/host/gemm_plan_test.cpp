@@ -46,7 +46,29 @@ static void partials_fit(const Model& m, bool bf16) {
   }
 }
 
+// All row counts of a block of 32 get the plan of its last one: a sequence's
+// sums keep their order when a row is added inside the block.
+static void plans_follow_blocks(const Model& m) {
+  const struct {
+    GemmRole role;
+    int N, K;
+  } shapes[] = {{GemmRole::kQkv, (m.H + 2 * m.KVH) * m.hd, m.d}, {GemmRole::kO, m.d, m.H * m.hd},
+                {GemmRole::kGateUp, 2 * m.F, m.d},               {GemmRole::kDown, m.d, m.F},
+                {GemmRole::kHead, 32000, m.d}};
+  for (const auto& s : shapes)
+    for (int M = 1; M <= kRows; ++M) {
+      const int E = (M + 31) / 32 * 32;
+      const GemmPath a = gemm_path(true, s.role, M, s.N, s.K), b = gemm_path(true, s.role, E, s.N, s.K);
+      CHECK(a == b, "%s role %d M=%d", m.name, (int)s.role, M);
+      if (a != GemmPath::kRowTile) continue;
+      const RtPlan p = row_tile_plan(s.role, M, s.N, s.K), q = row_tile_plan(s.role, E, s.N, s.K);
+      CHECK(p.rows == q.rows && p.cols == q.cols && p.ks == q.ks, "%s role %d M=%d: %dx%d/%d, M=%d: %dx%d/%d", m.name,
+            (int)s.role, M, p.rows, p.cols, p.ks, E, q.rows, q.cols, q.ks);
+    }
+}
+
 int main() {
+  for (const Model& m : kModels) plans_follow_blocks(m);
   for (const Model& m : kModels)
     for (bool bf16 : {true, false}) partials_fit(m, bf16);
   std::printf("ALL OK\n");
