@@ -1256,10 +1256,16 @@ __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
       const float* t = tl + r * kStride + j * 16;
       const float sc = row_scale(a.ss, a.ss_stride, m, a.K, a.eps);  // RMSNorm of the input row
       float v[8];
+      {
+        // h is rounded before its terms are split, as in gemm_prefill (which
+        // holds it in LDS): a product fused into the split's subtraction gives
+        // another last bit, and forwards of many rows take either kernel
+#pragma clang fp contract(off)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float gt = t[i] * sc, up = t[8 + i] * sc;
-        v[i] = gt / (1.0f + expf(-gt)) * up;
+        for (int i = 0; i < 8; ++i) {
+          const float gt = t[i] * sc, up = t[8 + i] * sc;
+          v[i] = gt / (1.0f + expf(-gt)) * up;
+        }
       }
       put_afrag<true, 2>(a.H, m, f, v, a.F >> 5, a.MBn);
     }

@@ -20,8 +20,10 @@ if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from paper_2606_12243_amd import via  # noqa: E402
+from paper_2606_12243_amd.session import Session  # noqa: E402
 from workload import configs, gen  # noqa: E402
 
+import gemm_plans  # noqa: E402
 from gpu_harness import Lockstep  # noqa: E402
 
 
@@ -115,6 +117,74 @@ def test_batched_prefill_lockstep(name, max_rows):
               f"tiers={sorted(ls.seen_tiers)} resyncs={len(ls.log)}", flush=True)
     finally:
         ls.close()
+
+
+# two layers of the 8B widths (small vocabulary)
+WIDTH_8B = dict(n_layers=2, d_model=4096, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=14336, vocab=700, dtype="bf16",
+                rms_eps=1e-5, rope_theta=10000.0)
+
+
+def device_weights(m, seed):
+    """N(0, 0.02) weights and unit gains, made on the device."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    d, hd, L = m["d_model"], m["head_dim"], range(m["n_layers"])
+
+    def mat(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=g)
+
+    ones = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    return dict(embed=mat(m["vocab"], d), lm_head=mat(m["vocab"], d), final_norm=ones, attn_norm=[ones for _ in L],
+                ffn_norm=[ones for _ in L], w_qkv=[mat((m["n_heads"] + 2 * m["n_kv_heads"]) * hd, d) for _ in L],
+                w_o=[mat(d, m["n_heads"] * hd) for _ in L], w_gate_up=[mat(2 * m["d_ffn"], d) for _ in L],
+                w_down=[mat(d, m["d_ffn"]) for _ in L])
+
+
+def prefilled(model, m, prompts, batched):
+    """Full-cache K and V of the prompts' valid slots, [layer, KV head, slot, dim] each."""
+    per = max(len(t) for t in prompts.values()) // via.BLOCK + 2
+    kv = via.KV(model, max_seqs=len(prompts), max_blocks_per_seq=per, blocks_full=per * len(prompts),
+                blocks_slim=per * len(prompts), max_rows=sum(len(t) for t in prompts.values()), max_batch=len(prompts),
+                max_drafts=1)
+    try:
+        sess = Session(model, kv, via.tier_params(0.9, 0.5, 1.0))
+        if batched:
+            sess.prefill_batch(prompts)
+        else:
+            for b, toks in prompts.items():
+                sess.prefill(b, toks)
+        torch.cuda.synchronize()
+        pool, L, H, hd = kv.pool_view(via.CACHE_FULL), m["n_layers"], m["n_kv_heads"], m["head_dim"]
+        out = {}
+        for b in prompts:
+            n, table = kv.seq_info(b, via.CACHE_FULL)
+            x = pool[:, :, torch.tensor(table, device="cuda")]
+            k = x[:, :, :, 0].reshape(L, H, len(table), hd // 8, 16, 8).transpose(3, 4).reshape(L, H, -1, hd)
+            v = x[:, :, :, 1].reshape(L, H, len(table), hd, 16).transpose(3, 4).reshape(L, H, -1, hd)
+            out[b] = (k[:, :, :n].clone(), v[:, :, :n].clone())
+        return out
+    finally:
+        kv.close()
+
+
+@pytest.mark.parametrize("m,lens,mixed", [(WIDTH_8B, (2060, 2100), "gate_up")])
+def test_batched_prefill_bits(m, lens, mixed):
+    """Forwards of many rows sum every projection in one order, whichever
+    kernel the row count takes (`mixed`: a projection that takes different ones
+    alone and batched): a prompt's K/V are the same bits either way.  At these
+    widths the attention takes one key split throughout."""
+    print(f"[case] prefill bits d={m['d_model']} lens={lens}", flush=True)
+    prompts = {b: gen.context_tokens(dict(model=m, seed_c=41), b, n + 1) for b, n in enumerate(lens)}
+    if mixed:
+        assert len({gemm_plans.path(m, mixed, M) for M in (*lens, sum(lens))}) > 1
+    model = via.Model(m, device_weights(m, 43), list(range(m["n_layers"])))
+    try:
+        alone, batch = prefilled(model, m, prompts, False), prefilled(model, m, prompts, True)
+        for b in prompts:
+            for x, y in zip(alone[b], batch[b]):
+                assert x.shape[2] == lens[b]
+                assert torch.equal(x.view(torch.int16), y.view(torch.int16)), f"prompt {b}"
+    finally:
+        model.close()
 
 
 def test_batched_prefill_is_all_or_nothing():
