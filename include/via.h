@@ -298,9 +298,12 @@ via_status via_prefill(via_model *m, via_kv *kv, int32_t seq_id, const int32_t *
  * prompts continue in later forwards), so the projections of a batch of
  * prompts run as one tall GEMM.  All-or-nothing: on any error no sequence
  * is attached (EINVAL for repeated or attached ids, ENOMEM when the pools
- * lack the blocks).  The results are those of one via_prefill per sequence,
- * to rounding: the projections sum in one order in forwards of more than
- * 2048 rows, in an order that follows the row count below. */
+ * lack the blocks).  Same results as one via_prefill per sequence when
+ * every forward has more than 512 rows either way: the projections then sum
+ * in one order.  (The attention's key splits follow the work of the whole
+ * forward; it takes one, so that the bits are the same, where that fills the
+ * GPU, at 32 heads for prompts of 384 to 6144 tokens that fit a forward.
+ * Elsewhere the results agree to rounding.) */
 via_status via_prefill_batch(via_model *m, via_kv *kv, int32_t n_seqs, const int32_t *seq_ids, const int32_t *lens,
                              const int32_t *tokens, void *stream);
 /* Route index at which the last full-verifier forward of the current (or

@@ -1041,7 +1041,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_prefill(GemmArgs a, int nt) 
 // WN = 2, KG = 2 (128 columns): up to 128 rows it keeps ~256 work-groups on the
 // weight stream, above it is taken where 256 columns would leave compute
 // units idle; waves 0-3 multiply the even and 4-7 the odd K steps and the two
-// halves are added in LDS.  WN = 4, KG = 1 (256 columns): the fewest copied
+// halves are added in LDS.  WN = 2, KG = 1: the same tiles with four waves that
+// take every K step, in the order of the 256-column and the prefill tiles, for
+// forwards of more than kFixedOrderRows rows; the copies bound both (1B shape,
+// 1023 rows, down projection: 58 us without a K split; with four, which make the
+// order follow the row count, 40 and 3 more in the residual update).  WN = 4, KG = 1 (256 columns): the fewest copied
 // bytes per product.
 //
 // kPart writes one fp32 partial per split, kSwiglu (the gate/up projection)
@@ -1278,8 +1282,11 @@ void launch_row_tile(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t
   const RtPlan p = row_tile_plan(role, a.M, a.N, a.K);
   const int ntiles = ((a.M + p.rows - 1) / p.rows) * ((a.N + p.cols - 1) / p.cols) * a.ksplit;
   const dim3 grid((ntiles + 7) / 8 * 8);
+  // 128 columns: one K group where the order of summation is fixed
+  const bool one = a.M > kFixedOrderRows && p.cols == 128;
+  const int threads = one ? 256 : 512;
   auto pick = [&](auto part, auto swiglu, auto stats) {
-    launch_timed(role == GemmRole::kGateUp ? swiglu : role == GemmRole::kHead ? stats : part, grid, 512, a, s, e0, e1);
+    launch_timed(role == GemmRole::kGateUp ? swiglu : role == GemmRole::kHead ? stats : part, grid, threads, a, s, e0, e1);
   };
 #define VIA_RT_PICK(...)                                                                        \
   pick(gemm_row_tile<__VA_ARGS__, Epi::kPart>, gemm_row_tile<__VA_ARGS__, Epi::kSwiglu>,   \
@@ -1288,6 +1295,12 @@ void launch_row_tile(GemmRole role, const GemmArgs& a, hipStream_t s, hipEvent_t
     VIA_RT_PICK(6, 4, 1, 5, 6);
   else if (p.cols == 256)
     VIA_RT_PICK(8, 4, 1, 5, 5);
+  else if (one && p.rows == 64)
+    VIA_RT_PICK(4, 2, 1, 6, 12);
+  else if (one && p.rows == 96)
+    VIA_RT_PICK(6, 2, 1, 5, 12);
+  else if (one)
+    VIA_RT_PICK(8, 2, 1, 5, 10);
   else if (p.rows == 64)
     VIA_RT_PICK(4, 2, 2, 3, 6);
   else if (p.rows == 96)

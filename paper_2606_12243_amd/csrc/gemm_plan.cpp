@@ -31,7 +31,6 @@ RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
   const bool split = role != GemmRole::kGateUp && role != GemmRole::kHead && M <= kFixedOrderRows;
   RtPlan best{0, 0, 0, 0.0};
   for (const Tile& tl : kTiles) {
-    if (M > kFixedOrderRows && tl.cols == 128) continue;  // its two K halves are another order
     const int tiles = ceil_div(M, tl.rows) * ceil_div(N, tl.cols);
     for (int ks = 1; ks <= (split ? 8 : 1) && (ks == 1 || K / 32 >= 16 * ks); ks *= 2) {
       const double us = 10.0 + tl.us * ceil_div(tiles * ks, 256) * K / (4096.0 * ks) + ks * partial_us(M, N);

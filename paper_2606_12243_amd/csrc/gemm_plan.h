@@ -23,9 +23,10 @@ enum class GemmRole { kQkv, kO, kGateUp, kDown, kHead };
 enum class GemmPath { kStream, kRowTile, kPrefill, kHead, kF32 };
 GemmPath gemm_path(bool bf16, GemmRole role, int M, int N, int K);
 
-// Forwards of more rows than this sum every projection in one order, so that a
-// row's result does not depend on the rows it is batched with.
-constexpr int kFixedOrderRows = 2048;
+// Forwards of more rows than this sum every projection in one order (no K
+// splits, K steps one after another), so that a row's result does not depend on
+// the rows it is batched with.
+constexpr int kFixedOrderRows = 512;
 // Tile of the prefill kernel.
 constexpr int kPfBM = 256, kPfBN = 256;
 

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
   put_afrag<BF16, NT>(Y, out, k0, v, d >> 5, MBn);
 }
 
-// Many-row form of the residual update (KS partials P, no head rows or
+// Many-row form of the residual update (one partial P, no head rows or
 // embedding gather): a work-group of four waves owns one 16-row block of the
 // fragment layout and one kNormChunk of columns.  Thread t of a wave takes row
 // t % 16 and, in each of the wave's K32 steps s = wave + 4 i, the 8-column group
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64) void resid_add_kernel(float* X, const float* P,
 // resid_add_kernel: the 8-column group 4 s + t / 16 is that kernel's thread,
 // and its partial sums of squares are added in that kernel's wave_sum order
 // (two levels within the thread, two across waves, two across lanes).
-template <int NT, int KS>
+template <int NT>
 __global__ __launch_bounds__(256) void resid_add_rows_kernel(float* X, const float* P, int M, int d, const uint16_t* g,
                                                              void* Y, int MBn, float* ss, int ss_stride, float* Xcopy,
                                                              const RowInfo* erows) {
@@ -189,7 +189,6 @@ __global__ __launch_bounds__(256) void resid_add_rows_kernel(float* X, const flo
   const int chunk = blockIdx.x, w = threadIdx.x >> 6, t = threadIdx.x & 63, r = t & 15, j = t >> 4;
   const int m = blockIdx.y * 16 + r;
   const bool live = m < M;
-  const size_t stride = (size_t)M * d;
   if (Xcopy && live) {
     const int xr = erows ? erows[m].xs : m;
     Xcopy = xr < 0 ? nullptr : Xcopy + (size_t)xr * d;
@@ -202,29 +201,17 @@ __global__ __launch_bounds__(256) void resid_add_rows_kernel(float* X, const flo
     if (!live || k0 >= d) continue;
     float* x = X + (size_t)m * d + k0;
     const float* a = P + (size_t)m * d + k0;
-    float4 b[KS][2];
-#pragma unroll
-    for (int q = 0; q < KS; ++q) {
-      b[q][0] = *(const float4*)(a + q * stride);
-      b[q][1] = *(const float4*)(a + q * stride + 4);
-    }
+    const float4 b[2] = {*(const float4*)a, *(const float4*)(a + 4)};
     float v[8], gain[8];
     float4 xv[2] = {*(float4*)x, *(float4*)(x + 4)};
     load_gain8(g + k0, gain);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      float4 u = xv[h], s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int q = 0; q < KS; ++q) {
-        s.x += b[q][h].x;
-        s.y += b[q][h].y;
-        s.z += b[q][h].z;
-        s.w += b[q][h].w;
-      }
-      u.x = u.x + s.x;
-      u.y = u.y + s.y;
-      u.z = u.z + s.z;
-      u.w = u.w + s.w;
+      float4 u = xv[h];
+      u.x = u.x + (0.f + b[h].x);
+      u.y = u.y + (0.f + b[h].y);
+      u.z = u.z + (0.f + b[h].z);
+      u.w = u.w + (0.f + b[h].w);
       *(float4*)(x + 4 * h) = u;
       if (Xcopy) *(float4*)(Xcopy + k0 + 4 * h) = u;
       v[4 * h + 0] = u.x;
@@ -617,18 +604,10 @@ void launch_resid_add(bool bf16, float* X, const float* P, int ksplit, int M, in
                       const RowInfo* rows, float* ss, int ss_stride, hipStream_t s, float* Xcopy, const void* E,
                       const RowInfo* erows) {
   const dim3 grid((d + kNormChunk - 1) / kNormChunk, M);
-  if (bf16 && P && !rows && !E && M > kManyRows && (ksplit == 1 || ksplit == 2 || ksplit == 4 || ksplit == 8)) {
+  if (bf16 && P && !rows && !E && M > kManyRows && ksplit == 1) {
     const dim3 rgrid((d + kNormChunk - 1) / kNormChunk, (M + 15) / 16);
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, rgrid, dim3(256), 0, s, X, P, M, d, (const uint16_t*)g, Y, MBn, ss, ss_stride, Xcopy,
-                         erows);
-    };
-    switch (ksplit) {
-      case 1: go(resid_add_rows_kernel<kTerms, 1>); break;
-      case 2: go(resid_add_rows_kernel<kTerms, 2>); break;
-      case 4: go(resid_add_rows_kernel<kTerms, 4>); break;
-      default: go(resid_add_rows_kernel<kTerms, 8>); break;
-    }
+    hipLaunchKernelGGL(resid_add_rows_kernel<kTerms>, rgrid, dim3(256), 0, s, X, P, M, d, (const uint16_t*)g, Y, MBn, ss,
+                       ss_stride, Xcopy, erows);
     return;
   }
   if (!bf16) {  // one partial

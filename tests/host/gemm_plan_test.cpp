@@ -28,7 +28,7 @@ constexpr Model kModels[] = {
     {"micro", 256, 4, 2, 64, 512, 17},      {"odd", 2112, 16, 4, 128, 4160, 17}, {"wide", 8192, 64, 8, 128, 28672, 17},
     {"narrow", 1024, 16, 16, 64, 8192, 17},
 };
-constexpr int kRows = kFixedOrderRows + 600;
+constexpr int kRows = 2600;  // past kFixedOrderRows and several of its tile counts
 
 // The workspace of a handle holds the partial products of every forward it
 // admits, not only of its largest.

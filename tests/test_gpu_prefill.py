@@ -119,7 +119,9 @@ def test_batched_prefill_lockstep(name, max_rows):
         ls.close()
 
 
-# two layers of the 8B widths (small vocabulary)
+# two layers of the 8B and the 1B widths (small vocabulary)
+WIDTH_1B = dict(n_layers=2, d_model=2048, n_heads=16, n_kv_heads=4, head_dim=128, d_ffn=5632, vocab=700, dtype="bf16",
+                rms_eps=1e-5, rope_theta=10000.0)
 WIDTH_8B = dict(n_layers=2, d_model=4096, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=14336, vocab=700, dtype="bf16",
                 rms_eps=1e-5, rope_theta=10000.0)
 
@@ -166,12 +168,13 @@ def prefilled(model, m, prompts, batched):
         kv.close()
 
 
-@pytest.mark.parametrize("m,lens,mixed", [(WIDTH_8B, (2060, 2100), "gate_up")])
+@pytest.mark.parametrize("m,lens,mixed", [(WIDTH_8B, (513, 600), None), (WIDTH_8B, (1023, 700), "gate_up"),
+                                          (WIDTH_8B, (2060, 2100), "gate_up"), (WIDTH_1B, (1023, 800), None)])
 def test_batched_prefill_bits(m, lens, mixed):
-    """Forwards of many rows sum every projection in one order, whichever
-    kernel the row count takes (`mixed`: a projection that takes different ones
-    alone and batched): a prompt's K/V are the same bits either way.  At these
-    widths the attention takes one key split throughout."""
+    """Forwards of more than 512 rows sum every projection in one order,
+    whichever tiles the row count takes (`mixed`: a projection that takes
+    different kernels alone and batched): a prompt's K/V are the same bits
+    either way.  At these sizes the attention takes one key split throughout."""
     print(f"[case] prefill bits d={m['d_model']} lens={lens}", flush=True)
     prompts = {b: gen.context_tokens(dict(model=m, seed_c=41), b, n + 1) for b, n in enumerate(lens)}
     if mixed:
