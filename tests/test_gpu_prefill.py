@@ -1,13 +1,18 @@
-"""The prefill GEMM: the compute-bound tile kernel that runs every projection
-of a forward of more than 512 rows.
+"""Prefill-sized forwards, and the prefill GEMM: the compute-bound tile kernel
+that runs a projection where the rows fill the GPU with 256 x 256 tiles.
 
 * via_gemm_bf16 (one activation term) against a float64 product of the same
   bf16 operands, within the rigorous bound of fp32 accumulation of exact bf16
   products, |err| <= K * 2^-24 * (|X| |W|^T); shapes cover one row, ragged
   M/N tails of the 256 x 256 tiles, K of one stage, and full prefill sizes.
-* A prefill-sized forward (prompts of 600 and 514 tokens, so the prefill GEMM
-  with its 2-term activations, and the SwiGLU epilogue of its gate/up tiles,
-  builds the caches), followed by lock-step decoding against the oracle.
+* One layer of the 8B widths at 4000 and 4160 rows, where the prefill GEMM with
+  its 2-term activations runs QKV, down and the gate/up projection with its
+  SwiGLU epilogue, against the oracle's fp64 logits of rows at the edges of the
+  tiles.
+* Prompts of 514 to 611 tokens of the small models (row tiles and the many-row
+  forms of the other kernels), alone and batched, followed by lock-step decoding
+  against the oracle.
+* A prompt's K/V alone and batched, bit for bit.
 """
 import ctypes as C
 
@@ -19,6 +24,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("needs a GPU", allow_module_level=True)
 
+from oracle.model import OracleModel  # noqa: E402
 from paper_2606_12243_amd import via  # noqa: E402
 from paper_2606_12243_amd.session import Session  # noqa: E402
 from workload import configs, gen  # noqa: E402
@@ -84,8 +90,8 @@ def test_prefill_sized_forward_lockstep(name):
     print(f"[case] prefill-sized forward {name}", flush=True)
     ls = Lockstep(cfg, max_rows=640, max_batch=2, max_drafts=8, max_blocks=48, blocks=192)
     try:
-        ls.add_prompt(0, gen.context_tokens(cfg, 0, 600))  # 599 rows per forward: ragged 256-row tiles
-        ls.add_prompt(1, gen.context_tokens(cfg, 1, 514))  # 513 rows: just past the threshold
+        ls.add_prompt(0, gen.context_tokens(cfg, 0, 600))  # 599 rows per forward: ragged row tiles
+        ls.add_prompt(1, gen.context_tokens(cfg, 1, 514))  # 513 rows: just past the many-row forms' threshold
         steps = ls.run_chain([0, 1], G=16, k=6)
         print(f"[done] {name} steps={steps} max_logit_err={ls.max_logit_err:.3g} tiers={sorted(ls.seen_tiers)} "
               f"resyncs={len(ls.log)}", flush=True)
@@ -139,6 +145,44 @@ def device_weights(m, seed):
                 ffn_norm=[ones for _ in L], w_qkv=[mat((m["n_heads"] + 2 * m["n_kv_heads"]) * hd, d) for _ in L],
                 w_o=[mat(d, m["n_heads"] * hd) for _ in L], w_gate_up=[mat(2 * m["d_ffn"], d) for _ in L],
                 w_down=[mat(d, m["d_ffn"]) for _ in L])
+
+
+@pytest.mark.parametrize("M,roles", [(4000, ("down", "gate_up")), (4160, ("qkv",))])
+def test_prefill_tiles_match_oracle(M, roles):
+    """A teacher-forced window of M rows through one layer of the 8B widths;
+    `roles` run on the prefill GEMM."""
+    print(f"[case] prefill tiles M={M} {roles}", flush=True)
+    m = dict(WIDTH_8B, n_layers=1)
+    for r in roles:
+        assert gemm_plans.path(m, r, M) == "prefill"
+    W = device_weights(m, 47)
+    tokens = gen.context_tokens(dict(model=m, seed_c=48), 0, M)
+    rows = sorted({r for t in (0, 128, 256, 512, 2048, M // 256 * 256, M) for r in (t - 1, t, t + 1) if 0 <= r < M})
+    # the oracle: K/V of every row, the rest of the layer for the rows compared
+    om = OracleModel(m, {k: [t.cpu() for t in v] if isinstance(v, list) else v.cpu() for k, v in W.items()})
+    x, pos = om.embed(tokens), torch.arange(M)
+    q, k, v = om.qkv(om.rmsnorm(x, om.w("attn_norm", 0)), 0, pos)
+    at = torch.tensor(rows)
+    x = x[at] + om.linear(om.attend(q[at], k, v, pos[None, :] <= at[:, None]), "w_o", 0)
+    ref = om.head(x + om.ffn(x, 0))
+    model = via.Model(m, W, [0])
+    blocks = M // via.BLOCK + 1
+    kv = via.KV(model, max_seqs=1, max_blocks_per_seq=blocks, blocks_full=blocks, blocks_slim=1, max_rows=M,
+                max_batch=1, max_drafts=1)
+    try:
+        via.check(via.via_kv_seq_reserve(kv.h, 0, 0))
+        out = via.Out(1, M, 1, m["vocab"], logits=True)
+        w = via.WindowBuf([0], [tokens], [[]], [[]], max_drafts=1)
+        p = via.tier_params(0.9, 0.5, 1.0)
+        via.check(via.via_verify_probe(model.h, kv.h, via.CACHE_FULL, C.byref(w.c), C.byref(p), C.byref(out.c),
+                                       via.stream_ptr()))
+        torch.cuda.synchronize()
+        err = (out.logits.view(M, -1)[at.cuda()].cpu().double() - ref).abs().max().item()
+        print(f"[done] max |err| {err:.3g} (logits' std {ref.std().item():.3g})", flush=True)
+        assert err < 2e-2  # the lock-step tests' bound for bf16 models
+    finally:
+        kv.close()
+        model.close()
 
 
 def prefilled(model, m, prompts, batched):
