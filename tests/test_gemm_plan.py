@@ -15,6 +15,8 @@ import pytest
 from paper_2606_12243_amd import via
 from workload import configs
 
+import row_tile_cases
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_12243_amd", "csrc")
 
@@ -39,3 +41,10 @@ def test_workspace_grows_with_max_rows(name):
     sizes = [via.via_workspace_bytes(C.byref(d), r, 4, 8, 8, 4) for r in range(1, 700)]
     assert sizes[0] > 0
     assert [r + 1 for r in range(1, len(sizes)) if sizes[r] < sizes[r - 1]] == []
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_gpu_cases_reach_every_row_tile_form():
+    """The sizes that the GPU tests run take every (tile, K groups, epilogue) the library holds."""
+    taken = set().union(*(row_tile_cases.forms(n, r) for n, r in row_tile_cases.CASES))
+    assert taken == row_tile_cases.ALL_FORMS

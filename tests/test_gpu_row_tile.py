@@ -2,13 +2,16 @@
 rows x 128 or 256 columns, 1 to 8 K splits) and the many-row residual update:
 probe forwards of a teacher-forced window against the oracle's fp64 logits.
 
-Row counts sit at the edges of the tiles (33, 64 | 65, 96 | 97, 128 | 129) and
-past them, where two or more row tiles and the 256-column tiles are taken; one
-model has ragged column tails (vocabulary 3001, FFN 1408) and no split, the
-other splits its K (2112 and 4160, whose last split is the shortest) 2 to 8
-ways.  Tolerance: the bf16 logit bound of the lock-step tests (2e-2), which
-covers the 2-term activations and the bf16 cache; logits here have a standard
-deviation of about 0.9.
+* Row counts at the edges of the tiles (33, 64 | 65, 96 | 97, 128 | 129) and
+  past them, where two or more row tiles are taken; one model has ragged column
+  tails (vocabulary 3001, FFN 1408) and no split, the other splits its K (2112
+  and 4160, whose last split is the shortest) 2 to 8 ways.
+* Every tile form with every epilogue (tests/row_tile_cases.py).
+* Forwards of fewer rows than their handle is for.
+
+Tolerance: the bf16 logit bound of the lock-step tests (2e-2), which covers the
+2-term activations and the bf16 cache at logits of a standard deviation of about
+0.9; where it is smaller (0.3 at d = 256) the bound shrinks with it.
 """
 import ctypes as C
 import functools
@@ -25,25 +28,19 @@ from oracle.model import OracleModel  # noqa: E402
 from paper_2606_12243_amd import via  # noqa: E402
 from workload import configs, gen  # noqa: E402
 
+import row_tile_cases  # noqa: E402
+
 SPLIT = dict(name="split_k", seed_w=21, seed_c=22, route=[0],
              model=dict(n_layers=1, d_model=2112, n_heads=16, n_kv_heads=4, head_dim=128, d_ffn=4160, vocab=700,
                         dtype="bf16", rms_eps=1e-5, rope_theta=10000.0))
 
 
-# one layer of the 8B and the 1B widths (narrow FFN and vocabulary where they do not matter)
-WIDE = {
-    "width_8b": dict(name="width_8b", seed_w=31, seed_c=32, route=[0],
-                     model=dict(n_layers=1, d_model=4096, n_heads=32, n_kv_heads=8, head_dim=128, d_ffn=512, vocab=700,
-                                dtype="bf16", rms_eps=1e-5, rope_theta=10000.0)),
-    "width_1b": dict(name="width_1b", seed_w=33, seed_c=34, route=[0],
-                     model=dict(n_layers=1, d_model=2048, n_heads=16, n_kv_heads=4, head_dim=128, d_ffn=5632, vocab=700,
-                                dtype="bf16", rms_eps=1e-5, rope_theta=10000.0)),
-}
-
-
 @functools.lru_cache(maxsize=None)
 def models(name):
-    cfg = SPLIT if name == "split_k" else WIDE[name] if name in WIDE else dict(configs.get(name), seed_c=23)
+    if name in row_tile_cases.MODELS:
+        cfg = dict(name=name, seed_w=31, seed_c=32, route=[0], model=row_tile_cases.MODELS[name])
+    else:
+        cfg = SPLIT if name == "split_k" else dict(configs.get(name), seed_c=23)
     W = gen.model_weights(cfg)
     return cfg, via.Model(cfg["model"], W, list(range(cfg["model"]["n_layers"]))), OracleModel(cfg["model"], W)
 
@@ -66,7 +63,7 @@ def check_window(name, rows, max_rows):
         torch.cuda.synchronize()
         got = out.logits.view(rows, V).cpu().double()
         ref = oracle.forward_sequence(tokens)
-        assert (got - ref).abs().max().item() < 2e-2
+        assert (got - ref).abs().max().item() < 2e-2 * min(1.0, ref.std().item() / 0.9)
         # the row statistics are those of the logits written
         assert torch.equal(out.row_argmax.cpu().long(), got.argmax(1))
         assert torch.equal(out.row_max.cpu().double(), got.amax(1))
@@ -80,6 +77,12 @@ def check_window(name, rows, max_rows):
                                        for r in (33, 64, 65, 96, 97, 128, 129, 192, 193, 300, 520)])
 def test_window_logits_match_oracle(name, rows):
     print(f"[case] row tile {name} rows={rows}", flush=True)
+    check_window(name, rows, rows)
+
+
+@pytest.mark.parametrize("name,rows", row_tile_cases.CASES)
+def test_every_tile_form(name, rows):
+    print(f"[case] {name} rows={rows}: {sorted(row_tile_cases.forms(name, rows))}", flush=True)
     check_window(name, rows, rows)
 
 
