@@ -11,11 +11,11 @@
 // multiple of 32 the host picks so that the whole launch has about 192
 // work-groups, or more when that would take spans well past 4096 keys); a work-group streams its span and writes
 // one (max, sum, output) partial per query, and a combine kernel merges the
-// partials of a query in split order.  When every item has one split (long
-// forwards: prefills), the work-group applies the combine's arithmetic to its
-// one partial and writes the output itself, and no combine runs.  Visibility of slot p for row r:
-// p < vis_len[r], or p is a window slot whose bit is set in the row's tree
-// mask.
+// partials of a query in split order.  When every item has one split (forwards
+// of many rows, such as prefills, and contexts of up to kAttnDirectKeys keys),
+// the work-group applies the combine's arithmetic to its one partial and writes
+// the output itself, and no combine runs.  Visibility of slot p for row r:
+// p < vis_len[r], or p is a window slot whose bit is set in the row's tree mask.
 //
 // bf16 path: four waves per work-group; wave w takes the 32-key blocks
 // w, w+4, ... of the span and streams them with the loads of its next block

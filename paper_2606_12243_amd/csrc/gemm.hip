@@ -42,13 +42,13 @@ constexpr int kTileN = 8 * 16 * kNBW;   // columns per work-group tile (8 waves)
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// Work-group tile: 16*MB rows x (8 * 16 * NBW) columns, one K slice.  Wave
-// w owns NBW 16-column blocks and streams their packed W over the whole
-// slice in chunks of C steps, two chunks ahead of the one it multiplies;
-// the X fragments of a chunk are loaded one chunk ahead and staged once in
-// LDS (double-buffered), where all eight waves read them: X leaves L2 once
-// per work-group and no cross-wave reduction is needed.  Columns past N are
-// computed from a clamped tile and never stored.
+// Work-group tile: the first 16*MB rows x (8 * 16 * NBW) columns over all of
+// K.  Wave w owns NBW 16-column blocks and streams their packed W in chunks of
+// C steps, two chunks ahead of the one it multiplies; the X fragments of a
+// chunk are loaded one chunk ahead and staged once in LDS (double-buffered),
+// where all eight waves read them: X leaves L2 once per work-group and no
+// cross-wave reduction is needed.  Columns past N are computed from a clamped
+// tile and never stored.
 template <int MB, int NT, int NBW, int C>
 struct TileShape {
   static constexpr int kCols = 8 * 16 * NBW;
@@ -56,9 +56,6 @@ struct TileShape {
   static constexpr int kXPT = kXChunk / kThreads;     // uint4 staged per thread
 };
 
-// `active` (wave-uniform) false: the wave helps stage X but loads no
-// weights and multiplies nothing (its accumulators stay zero).
-//
 // M32 (two 16-column blocks per wave, an even number of row blocks): the
 // products run on v_mfma_f32_32x32x16_bf16, twice the rate of the 16x16x32
 // form on this GPU.  Its operands are gathered from the same 1 KB
@@ -68,8 +65,7 @@ struct TileShape {
 // (2h + l/32)*16 + l%16.  acc is then f32x16[MB/2]: 32-row tile i holds
 // rows 32i + (r/4)*8 + (l/32)*4 + r%4, column l%32 of the wave's 32.
 template <int MB, int NT, int NBW, int C, bool M32 = false, typename Acc>
-__device__ void tile_bf16(const GemmArgs& a, int c0, int m0, int st_beg, int st_end, uint4* sx, Acc& acc,
-                          bool active = true) {
+__device__ void tile_bf16(const GemmArgs& a, int c0, uint4* sx, Acc& acc) {
   using TS = TileShape<MB, NT, NBW, C>;
   static_assert(TS::kXChunk % kThreads == 0, "chunk must split evenly over the threads");
   static_assert(!M32 || (NBW == 2 && MB % 2 == 0), "32x32 tiles need two column blocks and row-block pairs");
@@ -86,7 +82,7 @@ __device__ void tile_bf16(const GemmArgs& a, int c0, int m0, int st_beg, int st_
     const int pt = min(blk >> 2, t64 - 1);
     wt[j] = (const uint4*)a.W + (size_t)pt * S * 256 + (blk & 3) * 64 + (M32 ? fl + j * 32 : lane);
   }
-  const uint4* xg = (const uint4*)a.X + (size_t)(m0 >> 4) * 64;
+  const uint4* xg = (const uint4*)a.X;
   const size_t x_step = (size_t)a.MBn * 64, x_term = (size_t)S * x_step;
   if constexpr (M32) {
 #pragma unroll
@@ -99,23 +95,19 @@ __device__ void tile_bf16(const GemmArgs& a, int c0, int m0, int st_beg, int st_
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) acc[j][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const int nst = st_end - st_beg;
-  if (nst <= 0) return;
-  const int nch = (nst + C - 1) / C;
+  const int nch = (S + C - 1) / C;
 
 #define TILE_LOAD_W(w, ch)                                                  \
-  if (active) {                                                             \
-    _Pragma("unroll") for (int sc = 0; sc < C; ++sc) {                      \
-      const size_t st = (size_t)min(st_beg + (ch) * C + sc, st_end - 1);    \
-      _Pragma("unroll") for (int j = 0; j < NBW; ++j) w[sc][j] = wt[j][st * 256]; \
-    }                                                                       \
+  _Pragma("unroll") for (int sc = 0; sc < C; ++sc) {                        \
+    const size_t st = (size_t)min((ch) * C + sc, S - 1);                    \
+    _Pragma("unroll") for (int j = 0; j < NBW; ++j) w[sc][j] = wt[j][st * 256]; \
   }
 #define TILE_LOAD_X(ch)                                                     \
   {                                                                         \
     _Pragma("unroll") for (int u = 0; u < TS::kXPT; ++u) {                  \
       const int e = threadIdx.x + u * kThreads; /* [step][term][mb][lane] */ \
       const int l = e & 63, mb = (e >> 6) % MB, q = (e / (64 * MB)) % NT, sc = e / (64 * MB * NT); \
-      const size_t st = (size_t)min(st_beg + (ch) * C + sc, st_end - 1);   \
+      const size_t st = (size_t)min((ch) * C + sc, S - 1);                 \
       xs[u] = xg[q * x_term + st * x_step + mb * 64 + l];                   \
     }                                                                       \
   }
@@ -125,8 +117,8 @@ __device__ void tile_bf16(const GemmArgs& a, int c0, int m0, int st_beg, int st_
     _Pragma("unroll") for (int u = 0; u < TS::kXPT; ++u) d[u * kThreads] = xs[u]; \
   }
 #define TILE_COMPUTE(w, ch)                                                 \
-  if (active) {                                                             \
-    const int valid = nst - (ch) * C;                                       \
+  {                                                                         \
+    const int valid = S - (ch) * C;                                         \
     if constexpr (M32) {                                                    \
       const uint4* xb = sx + ((ch) & 1) * TS::kXChunk + sel * 64 + fl;      \
       _Pragma("unroll") for (int sc = 0; sc < C; ++sc) {                    \
@@ -272,7 +264,7 @@ __global__ __launch_bounds__(kThreads) void gemm_head(GemmArgs a) {
     // 32x32x16 MFMAs: tile i, register r of lane l is row 32i + (r/4)*8 + (l/32)*4 + r%4,
     // column wave*32 + l%32 of the work-group's tile
     f32x16 acc[MB / 2];
-    tile_bf16<MB, kTerms, kNBW, C, true>(a, c0, 0, 0, a.K >> 5, (uint4*)smem, acc);
+    tile_bf16<MB, kTerms, kNBW, C, true>(a, c0, (uint4*)smem, acc);
     const int cl = wave * 32 + (lane & 31), rl = (lane >> 5) * 4;
     __syncthreads();  // the X buffers become the output tile
 #pragma unroll
@@ -281,7 +273,7 @@ __global__ __launch_bounds__(kThreads) void gemm_head(GemmArgs a) {
       for (int r = 0; r < 16; ++r) lds[(i * 32 + (r >> 2) * 8 + rl + (r & 3)) * kLdc + cl] = acc[i][r];
   } else {
     f32x4 acc[kNBW][MB];
-    tile_bf16<MB, kTerms, kNBW, C>(a, c0, 0, 0, a.K >> 5, (uint4*)smem, acc);
+    tile_bf16<MB, kTerms, kNBW, C>(a, c0, (uint4*)smem, acc);
     const int n = lane & 15, g = lane >> 4;
     __syncthreads();  // the X buffers become the output tile
 #pragma unroll
@@ -430,7 +422,6 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up_ki(GemmArgs a) {
   __shared__ __align__(16) float red[kWaves][16 * MB][NBM * 16 + 4];
   const int nblocks = a.N >> 4;
   const int blk0 = blockIdx.x * a.nb;
-  const int m0 = blockIdx.y * 16 * MB;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nb = min(a.nb, nblocks - blk0);
   const int S = a.K >> 5, t64 = (a.N + 63) >> 6;
@@ -440,7 +431,7 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up_ki(GemmArgs a) {
     const int blk = blk0 + min(j, nb - 1);
     wt[j] = (const uint4*)a.W + (size_t)min(blk >> 2, t64 - 1) * S * 256 + (blk & 3) * 64 + lane;
   }
-  const uint4* xg = (const uint4*)a.X + (size_t)(m0 >> 4) * 64 + lane;
+  const uint4* xg = (const uint4*)a.X + lane;
   const size_t x_step = (size_t)a.MBn * 64, x_term = (size_t)S * x_step;
   f32x4 acc[NBM][MB];
 #pragma unroll
@@ -491,9 +482,9 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up_ki(GemmArgs a) {
       for (int r = 0; r < 4; ++r) red[wave][mb * 16 + g * 4 + r][j * 16 + n] = acc[j][mb][r];
   __syncthreads();
   for (int e = threadIdx.x; e < 16 * MB * nb; e += kThreads) {
-    const int r = e / nb, j = e - r * nb, m = m0 + r;
-    if (m >= a.M) continue;
-    const float sc = row_scale(a.ss, a.ss_stride, m, a.K, a.eps);  // RMSNorm of the input row
+    const int r = e / nb, j = e - r * nb;
+    if (r >= a.M) continue;
+    const float sc = row_scale(a.ss, a.ss_stride, r, a.K, a.eps);  // RMSNorm of the input row
     float v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -507,7 +498,7 @@ __global__ __launch_bounds__(kThreads) void gemm_gate_up_ki(GemmArgs a) {
       up *= sc;
       v[i] = gt / (1.0f + expf(-gt)) * up;
     }
-    put_afrag<true, NT>(a.H, m, (blk0 + j) * 8, v, a.F >> 5, a.MBn);
+    put_afrag<true, NT>(a.H, r, (blk0 + j) * 8, v, a.F >> 5, a.MBn);
   }
 }
 

@@ -20,8 +20,10 @@ double partial_us(int M, int N) { return 8e-6 / 3.0 * (ceil_div(M, 32) * 32) * (
 
 // The tile and split with the smallest estimate: rounds of tiles on 256 compute
 // units and every split's partial.  The time of a round per 4096 of K is measured
-// on the 8B gate/up projection (48, 96, 128, 160 and 256 rows).  Above kFixedOrderRows rows there is one split and one
-// order of summation (that of the prefill tiles too), whatever the row count.
+// on the 8B gate/up projection (48, 96, 128, 160 and 256 rows); QKV, O, down and
+// narrower models take it over, it was not measured on each of them.  Above
+// kFixedOrderRows rows there is one split and one order of summation (that of
+// the prefill tiles too), whatever the row count.
 RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
   struct Tile {
     int rows, cols;
