@@ -143,6 +143,10 @@ __global__ __launch_bounds__(kDimrThreads, 2 * PER_CU) void dimr_cost_kernel(Dim
     lq = lse_merge(lq, part[0][w]);
     lp = lse_merge(lp, part[1][w]);
   }
+  // an infinite logit makes log Z infinite (above, exp(inf - inf) made the sum a
+  // NaN, which the comparisons below would turn into a cost of 0)
+  if (lq.m == INFINITY) lq.s = 1.f;
+  if (lp.m == INFINITY) lp.s = 1.f;
   const float lzq = lq.m + logf(lq.s), lzp = lp.m + logf(lp.s);
 
   // second pass

@@ -88,6 +88,25 @@ def test_dimr_cost_at_kept_round_edges(rows, V, ld):
     assert ((got - ref).abs() <= 1e-5 * ref.abs() + 8 * 2.0 ** -23 * lmax * 2 + 1e-6).all()
 
 
+def test_dimr_cost_of_an_infinite_logit_is_not_a_number():
+    """A row of q that overflowed has no cost: NaN, as in fp64, and not the 0 of a
+    perfect mask.  Its neighbours keep theirs, and a token that p alone excludes
+    (-inf) costs what it does in fp64; bound as in test_dimr_cost_matches_fp64."""
+    print("[case] dimr_cost infinities", flush=True)
+    g = torch.Generator().manual_seed(5)
+    q = torch.randn(4, 3001, generator=g) * 2.0
+    p = q + torch.randn(4, 3001, generator=g)
+    lmax = (torch.cat([q, p]).abs().max().item() / 0.8 + math.log(3001)) * 2
+    q[1, 700] = float("inf")
+    q[2, 3000] = float("inf")  # among the ids past the last whole round
+    p[3, [0, 1, 2, 3, 2999]] = float("-inf")
+    got = gpu_cost(q, p, 0.8, 0.1, 1.1)
+    ref = rkl_cost(q.double(), p.double(), 0.8, 0.1, 1.1)
+    assert torch.isnan(ref[1:3]).all() and torch.isnan(got[1:3]).all()
+    tol = 1e-5 * ref.abs() + 8 * 2.0 ** -23 * lmax * 2 + 1e-6
+    assert ((got - ref).abs() <= tol)[[0, 3]].all(), (got, ref)
+
+
 def test_dimr_cost_rejects_bad_arguments():
     sp = C.c_void_p(0)
     buf = torch.zeros(64, dtype=torch.float32, device="cuda")
