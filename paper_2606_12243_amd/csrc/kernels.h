@@ -107,11 +107,21 @@ struct QkvArgs {
   int ss_stride, d;
   float eps;
   double2* rope;       // [M][hd/2] rotations (cos, sin) of the rows' positions
-                       // (forwards of more than kRopeOwnRows rows)
+                       // (read where qkv_rope_table says)
 };
-// Forwards of up to this many rows compute the rotations in every layer, others
-// once, into a.rope.
-constexpr int kRopeOwnRows = 32;
+// Whether a forward takes its rotations from a table, written once for all its
+// layers, and finishes QKV by tiles of 16 rows, or computes them in every layer, a
+// row and head at a time: up to 2304 (row, head) pairs the latter's work-groups run
+// side by side and the tiles' longer chain and the table's launch cost more.  A
+// window, table | own: 12 heads (width 512, 4 layers) 33 rows 253.5 | 247.4 us, 128
+// rows 265.4 | 260.5, 512 rows 327.9 | 333.4; 24 heads (1B widths, 4 layers) 33 rows
+// 326.6 | 318.0, 96 rows 363.0 | 354.3, 512 rows 674 | 687; 48 heads (8B widths, 4
+// layers) 33 rows 547.6 | 541.5, 128 rows 759 | 757, 512 rows 1820 | 1855.  Both
+// give the same bits.
+constexpr int kRopeOwnPairs = 2304;
+inline bool qkv_rope_table(const QkvArgs& a) {
+  return a.M > kManyRows || (a.M > 32 && a.M * (a.H + 2 * a.KVH) > kRopeOwnPairs);
+}
 void launch_rope_table(const QkvArgs& a, hipStream_t s);
 void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s);
 

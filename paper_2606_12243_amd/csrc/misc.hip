@@ -330,8 +330,8 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvArgs a) {
   qkv_store<T>(a, ri, m, hh, j, x1 * sc, x2 * sc, cs_sn.x, cs_sn.y);
 }
 
-// Rotations of the rows of a forward of more than kRopeOwnRows rows, computed
-// once for all its layers: grid (M), one thread per pair.
+// Rotations of the rows of a forward, computed once for all its layers: grid
+// (M), one thread per pair.
 __global__ __launch_bounds__(64) void rope_table_kernel(QkvArgs a) {
   const int m = blockIdx.x, j = threadIdx.x, half = a.hd >> 1;
   if (j >= half) return;
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64) void rope_table_kernel(QkvArgs a) {
   a.rope[(size_t)m * half + j] = cs_sn;
 }
 
-// The QKV finish of such forwards.  A work-group takes 16 consecutive rows and
+// The QKV finish with the rotations read from that table.  A work-group takes 16 consecutive rows and
 // one KV head's share of them, its G query heads, its K head and its V head (or,
 // where that leaves compute units idle, some of them).  Thread t holds row t / 16
 // and the 8 dims from (t % 16) * 8 (hd 64: two heads' worth at a time), so the
@@ -634,7 +634,7 @@ void launch_rope_table(const QkvArgs& a, hipStream_t s) {
 }
 
 void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
-  if (a.M > kRopeOwnRows && (a.ksplit == 1 || a.ksplit == 2 || a.ksplit == 4 || a.ksplit == 8)) {
+  if (qkv_rope_table(a) && (a.ksplit == 1 || a.ksplit == 2 || a.ksplit == 4 || a.ksplit == 8)) {
     const int tiles = (a.M + 15) / 16, heads = a.H / a.KVH + 2, passes = a.hd == 128 ? heads : (heads + 1) / 2;
     const dim3 grid(tiles, a.KVH, std::min(passes, (256 + tiles * a.KVH - 1) / (tiles * a.KVH)));
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
@@ -658,6 +658,7 @@ void launch_qkv_finish(bool bf16, const QkvArgs& a, hipStream_t s) {
       case 1: go(qkv_finish_kernel<uint16_t, 1>); break;
       case 2: go(qkv_finish_kernel<uint16_t, 2>); break;
       case 4: go(qkv_finish_kernel<uint16_t, 4>); break;
+      case 8: go(qkv_finish_kernel<uint16_t, 8>); break;
       default: go(qkv_finish_kernel<uint16_t, 0>); break;
     }
   } else {

@@ -401,7 +401,7 @@ via_status exec_forward(via_model* m, via_kv* kv, int cache, Plan& P, bool head,
   qa.d = D.d;
   qa.eps = eps;
   qa.rope = (double2*)(ws + L.rope);
-  if (M > kRopeOwnRows) launch_rope_table(qa, s);
+  if (qkv_rope_table(qa)) launch_rope_table(qa, s);
   for (size_t si = start_si; si < route.size(); ++si) {
     const int l = route[si];
     gemm(Yf, m->w_qkv[l], D.g_qkv, GemmRole::kQkv, VIA_KERNEL_QKV);
