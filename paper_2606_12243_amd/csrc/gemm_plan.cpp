@@ -21,7 +21,11 @@ double partial_us(int M, int N) { return 8e-6 / 3.0 * (ceil_div(M, 32) * 32) * (
 // The tile and split with the smallest estimate: rounds of tiles on 256 compute
 // units and every split's partial.  The time of a round per 4096 of K is measured
 // on the 8B gate/up projection (48, 96, 128, 160 and 256 rows); QKV, O, down and
-// narrower models take it over, it was not measured on each of them.  Above
+// narrower models take it over, it was not measured on each of them.  Up to 4
+// splits have at least 8 K steps each, 8 splits 16: the steps of a split run one
+// after another, and short K is all latency (a window, at least 16 | 8 steps: width
+// 512 33 rows 247 | 222 us, 128 rows 261 | 237; 1B widths, 8 splits of 8 steps, 33
+// rows 318 | 310 but 128 rows 374 | 381).  Above
 // kFixedOrderRows rows there is one split and one order of summation (that of
 // the prefill tiles too), whatever the row count.
 RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
@@ -34,7 +38,7 @@ RtPlan row_tile_plan(GemmRole role, int M, int N, int K) {
   RtPlan best{0, 0, 0, 0.0};
   for (const Tile& tl : kTiles) {
     const int tiles = ceil_div(M, tl.rows) * ceil_div(N, tl.cols);
-    for (int ks = 1; ks <= (split ? 8 : 1) && (ks == 1 || K / 32 >= 16 * ks); ks *= 2) {
+    for (int ks = 1; ks <= (split ? 8 : 1) && (ks == 1 || K / 32 >= (ks <= 4 ? 8 : 16) * ks); ks *= 2) {
       const double us = 10.0 + tl.us * ceil_div(tiles * ks, 256) * K / (4096.0 * ks) + ks * partial_us(M, N);
       if (!best.ks || us < best.us) best = RtPlan{tl.rows, tl.cols, ks, us};
     }

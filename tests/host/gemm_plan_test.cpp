@@ -67,7 +67,17 @@ static void plans_follow_blocks(const Model& m) {
     }
 }
 
+// A short K is split too where its tiles leave the GPU idle (512 columns or
+// fewer), into no less than 8 K steps.
+static void short_k_is_split() {
+  for (int K : {512, 1024, 1408, 2048}) {
+    const int ks = row_tile_plan(GemmRole::kO, 33, 512, K).ks;
+    CHECK(ks == (K >= 1024 ? 4 : 2), "K=%d: %d splits", K, ks);
+  }
+}
+
 int main() {
+  short_k_is_split();
   for (const Model& m : kModels) plans_follow_blocks(m);
   for (const Model& m : kModels)
     for (bool bf16 : {true, false}) partials_fit(m, bf16);
