@@ -1152,6 +1152,20 @@ __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
     __builtin_amdgcn_sched_group_barrier(0x008, 2, 0); /* 2 MFMAs */    \
   }                                                                      \
   if constexpr (kMma > 2 * kReads) __builtin_amdgcn_sched_group_barrier(0x008, kMma - 2 * kReads, 0);
+  // 256 columns, up to kFixedOrderRows rows: every kFlush K steps the products so
+  // far go to a second set of sums.  With fewer K splits than the kernels before
+  // and no K halves, up to 224 products added to one accumulator made the logits of
+  // 8B windows of 320 to 512 rows 10% less exact; so they are what they were, for
+  // 0-1% of the window.  (The gate/up projection never had splits; the head's
+  // and the longer forwards' order is fixed.)
+  constexpr bool kSums = WN == 4 && EPI == Epi::kPart;
+  constexpr int kFlush = 16;
+  const bool flush = kSums && a.M <= kFixedOrderRows;
+  f32x4 sum[kSums ? HB : 1][4];
+#pragma unroll
+  for (int i = 0; i < (kSums ? HB : 1); ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   int sx = 0, sw = 0;  // ring positions of the trip in registers
   auto next = [](int s, int n) { return s + 1 == n ? 0 : s + 1; };
   Ops pa, pb;
@@ -1182,7 +1196,23 @@ __global__ __launch_bounds__(128 * WN * KG, 1) void gemm_row_tile(GemmArgs a) {
     for (; t + 2 < T;) {
       VIA_RT_TRIP(pa, pb)
       VIA_RT_TRIP(pb, pa)
+      if constexpr (kSums)
+        if (flush && t % kFlush == 0) {
+#pragma unroll
+          for (int i = 0; i < HB; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              sum[i][j] += acc[i][j];
+              acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
     }
+    if constexpr (kSums)
+      if (flush)
+#pragma unroll
+        for (int i = 0; i < HB; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j] + acc[i][j];
     // one or two trips left; the last one of an odd split has no second K step
     const bool tail = s_beg + (T - 1) * KG + kg < s_end;
     if (T - t == 2) {
