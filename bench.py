@@ -659,7 +659,7 @@ def prefill_forward_roofline(cfg, W, n_seq=None, ctx=None, per_sequence=True):
             "one_sequence_per_call": None if ms_seq is None else {
                 "ms": round(ms_seq, 2),
                 "frac": round((gemm_flop + attn_flop) / (ms_seq * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)},
-            "note": "projections run as 2 bf16-term passes of the prefill GEMM (fp32-activation "
+            "note": "projections multiply 2 bf16 terms per activation (fp32-activation "
                     "contract); the frac counts each product's 2MNK once"}
 
 
